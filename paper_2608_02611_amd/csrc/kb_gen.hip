@@ -11,31 +11,27 @@
 // plus binary64 log/sqrt/sincos per normal pair).
 #include "kb_device.hpp"
 #include "kb_internal.hpp"
+#include "kb_math.hpp"
 
 namespace kb {
 namespace {
 
-constexpr double kTwoPi = 6.283185307179586476925286766559;  // 2 pi rounded to binary64
-
 __device__ __forceinline__ float u01(uint32_t x) { return (float)(x >> 8) * 0x1p-24f; }
 
-// Box-Muller on one word pair in binary64: the cosine and sine branches
-// rho cos(theta), rho sin(theta) with rho = sqrt(-2 ln u1), theta = 2 pi u2.
-__device__ __forceinline__ void box_muller64(uint32_t xa, uint32_t xb, double& zc, double& zs) {
-    const double u1 = ((double)xa + 1.0) * 0x1p-32;  // (0, 1]
-    const double u2 = (double)xb * 0x1p-32;          // [0, 1)
-    const double rho = sqrt(-2.0 * log(u1));
-    const double theta = kTwoPi * u2;
-    double s, c;
-    sincos(theta, &s, &c);
-    zc = rho * c;
-    zs = rho * s;
-}
+// The device's seeds for the binary64 functions (v_rcp_f64 and v_rsq_f64 are
+// good to about 2^-24).
+struct DeviceSeed {
+    static __device__ __forceinline__ double rcp(double x) { return __builtin_amdgcn_rcp(x); }
+    static __device__ __forceinline__ double rsq(double x) { return __builtin_amdgcn_rsq(x); }
+    static __device__ __forceinline__ double frexp_mant(double x) { return __builtin_amdgcn_frexp_mant(x); }
+    static __device__ __forceinline__ int frexp_exp(double x) { return __builtin_amdgcn_frexp_exp(x); }
+    static __device__ __forceinline__ double ldexp(double x, int n) { return __builtin_ldexp(x, n); }
+};
 
-// The same, each branch rounded once to binary32.
+// Box-Muller on one word pair, each branch rounded once to binary32.
 __device__ __forceinline__ void box_muller(uint32_t xa, uint32_t xb, float& zc, float& zs) {
     double c, s;
-    box_muller64(xa, xb, c, s);
+    box_muller64<DeviceSeed>(xa, xb, c, s);
     zc = (float)c;
     zs = (float)s;
 }
@@ -132,8 +128,8 @@ hipError_t launch_typed(void* dst, uint64_t n, float p0, float p1, uint64_t seed
 // chi-square over its degrees of freedom), rounded once to binary32.
 __device__ __forceinline__ float student_t3(u32x4 w) {
     double z0, z1, z2, z3;
-    box_muller64(w.x, w.y, z0, z1);
-    box_muller64(w.z, w.w, z2, z3);
+    box_muller64<DeviceSeed>(w.x, w.y, z0, z1);
+    box_muller64<DeviceSeed>(w.z, w.w, z2, z3);
     const double chi2 = (z1 * z1 + z2 * z2) + z3 * z3;
     return (float)(z0 / sqrt(chi2 / 3.0));
 }

@@ -1,0 +1,85 @@
+// Checks the generator's binary64 functions (kb_math.hpp) on the host against
+// 80-bit long double: the largest error of each, in units in the last place
+// of binary64, on the ends of every reduction interval and on words spread
+// over the range.  The seeds are off by 2^-23 either way, twice what the
+// device's reciprocal and inverse square root instructions may be off.
+// Prints one line per function: name, largest error, word (pair) it was at.
+#include <cmath>
+#include <cstdio>
+#include <vector>
+
+#include "../paper_2608_02611_amd/csrc/kb_math.hpp"
+
+namespace {
+
+template <int SIGN>
+struct Seed {
+    static constexpr double off = 1.0 + SIGN * 0x1p-23;
+    static double rcp(double x) { return 1.0 / x * off; }
+    static double rsq(double x) { return 1.0 / std::sqrt(x) * off; }
+    static double frexp_mant(double x) { int e; return std::frexp(x, &e); }
+    static int frexp_exp(double x) { int e; std::frexp(x, &e); return e; }
+    static double ldexp(double x, int n) { return std::ldexp(x, n); }
+};
+
+// |got - want| in units in the last place of binary64 at want.
+double ulps(double got, long double want) {
+    if (want == 0.0L) return got == 0.0 ? 0.0 : 1e300;
+    int e;
+    std::frexp((double)want, &e);
+    return (double)(std::fabs((long double)got - want) / std::ldexp(1.0L, e - 53));
+}
+
+struct Worst {
+    double u = 0.0;
+    uint32_t at = 0;
+    void see(double v, uint32_t x) {
+        if (!(v <= u)) { u = v; at = x; }
+    }
+};
+
+template <int SIGN>
+void check(const std::vector<uint32_t>& words) {
+    using S = Seed<SIGN>;
+    Worst lg, root, sn, cs;
+    for (uint32_t x : words) {
+        const double t = kb::neg2_log_u01<S>(x);
+        // (log1p keeps the accuracy of the oracle value itself near u = 1)
+        const long double m = (long double)x + 1.0L;
+        const long double want = -2.0L * (x > 0xF0000000u ? log1pl((m - 0x1p32L) * 0x1p-32L) : logl(m * 0x1p-32L));
+        lg.see(ulps(t, want), x);
+        root.see(ulps(kb::math_sqrt<S>(t), sqrtl((long double)t)), x);
+        double s, c;
+        kb::sincos_2pi_u(x, s, c);
+        const double theta = 6.283185307179586476925286766559 * ((double)x * 0x1p-32);
+        sn.see(ulps(s, sinl((long double)theta)), x);
+        cs.see(ulps(c, cosl((long double)theta)), x);
+    }
+    std::printf("neg2_log %.3f %08x\nsqrt %.3f %08x\nsin %.3f %08x\ncos %.3f %08x\n", lg.u, lg.at, root.u, root.at,
+                sn.u, sn.at, cs.u, cs.at);
+}
+
+}  // namespace
+
+int main() {
+    std::vector<uint32_t> words;
+    // every power of two and every eighth of the circle, with neighbours
+    for (int k = 0; k < 32; ++k)
+        for (int d = -70; d <= 70; ++d) words.push_back((1u << k) + (uint32_t)d);
+    for (uint32_t o = 0; o < 16; ++o)
+        for (int d = -70; d <= 70; ++d) words.push_back((o << 28) + (uint32_t)d);
+    // sqrt(1/2) of every binade, where the logarithm changes its exponent
+    for (int k = 1; k < 33; ++k) {
+        const uint32_t m = (uint32_t)(0.70710678118654752 * std::ldexp(1.0, k));
+        for (int d = -70; d <= 70; ++d) words.push_back(m + (uint32_t)d);
+    }
+    uint64_t s = 0x9E3779B97F4A7C15ull;
+    for (int i = 0; i < 1000000; ++i) {
+        s ^= s << 13; s ^= s >> 7; s ^= s << 17;  // xorshift64
+        words.push_back((uint32_t)(s >> 32));
+        words.push_back((uint32_t)(s >> 32) >> (s & 31));
+    }
+    check<1>(words);
+    check<-1>(words);
+    return 0;
+}
