@@ -16,11 +16,20 @@ enum : int { DT_F32 = 0, DT_F16 = 1, DT_BF16 = 2, DT_U32 = 3 };
 // M0*x0 and M1*x2 are split into (hi, lo); the new state is
 // (hi1 ^ x1 ^ k0, lo1, hi0 ^ x3 ^ k1, lo0); the key gains (W0, W1) mod 2^32
 // between rounds.  mul_hi and the low product map to one
-// v_mad_u64_u32 each.
+// v_mad_u64_u32 each, the two exclusive ors to one v_bitop3_b32 (0x96 is the
+// truth table of a ^ b ^ c; the key is wave-uniform and stays in a scalar
+// register).  The multiplies issue at a quarter rate, so a block costs about
+// 100 full-rate instructions; as two exclusive ors each it cost 120 (3 x 33.5
+// million fp16 normals 170 -> 157 us, a whole block per element in the
+// planted changes of 16.8 million fp32 elements 38 -> 33 us).
 // ---------------------------------------------------------------------------
 struct u32x4 {
     uint32_t x, y, z, w;
 };
+
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+    return (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b, (int)c, 0x96);
+}
 
 __device__ __forceinline__ u32x4 philox4x32_10(u32x4 ctr, uint32_t k0, uint32_t k1) {
     constexpr uint32_t M0 = 0xD2511F53u, M1 = 0xCD9E8D57u;
@@ -30,9 +39,9 @@ __device__ __forceinline__ u32x4 philox4x32_10(u32x4 ctr, uint32_t k0, uint32_t 
         const uint64_t p0 = (uint64_t)M0 * ctr.x;
         const uint64_t p1 = (uint64_t)M1 * ctr.z;
         u32x4 nxt;
-        nxt.x = (uint32_t)(p1 >> 32) ^ ctr.y ^ k0;
+        nxt.x = xor3((uint32_t)(p1 >> 32), ctr.y, k0);
         nxt.y = (uint32_t)p1;
-        nxt.z = (uint32_t)(p0 >> 32) ^ ctr.w ^ k1;
+        nxt.z = xor3((uint32_t)(p0 >> 32), ctr.w, k1);
         nxt.w = (uint32_t)p0;
         ctr = nxt;
         k0 += W0;

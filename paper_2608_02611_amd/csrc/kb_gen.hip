@@ -78,6 +78,7 @@ __global__ __launch_bounds__(256) void gen_kernel(void* __restrict__ dst, uint64
                                                   uint64_t n_blocks) {
     const float width = p1 - p0;  // binary32, one rounding
     const uint64_t end = offset + n;
+    const uint64_t n_whole = (offset & 3u) == 0 ? n >> 2 : 0;
     const uint64_t step = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n_blocks; t += step) {
         const uint64_t b = b_first + t;
@@ -95,10 +96,12 @@ __global__ __launch_bounds__(256) void gen_kernel(void* __restrict__ dst, uint64
 #pragma unroll
             for (int i = 0; i < 4; ++i) v[i] = fmaf(z[i], p1, p0);
         }
-        const uint64_t g0 = 4 * b;
-        if (g0 >= offset && g0 + 4 <= end && ((g0 - offset) & 3) == 0) {
-            store_four<DT>(dst, g0 - offset, v, w);
+        // (offset a multiple of 4: block t is the output's elements 4 t ..
+        // 4 t + 3, all of them inside for t < n / 4)
+        if (t < n_whole) {
+            store_four<DT>(dst, 4 * t, v, w);
         } else {
+            const uint64_t g0 = 4 * b;
             const uint32_t words[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
             for (int i = 0; i < 4; ++i) {

@@ -7,9 +7,10 @@
 // Box-Muller pair takes about 70 binary64 operations this way, where the
 // general functions took about 300 (the generator is bound by instruction
 // issue, not by memory; 3 x 33.5 million fp16 normals: 297 -> 170 us, the
-// Student-t of 16.8 million elements: 245 -> 150 us).  Each function is within 2.6 units in the last place
-// of binary64, so the binary32 rounding of a result moves about as rarely as
-// between two general libraries (a few in 10^8).
+// Student-t of 16.8 million elements: 245 -> 150 us).  Each function is
+// within 2.6 units in the last place of binary64, so the binary32 rounding of
+// a result moves about as rarely as between two general libraries (a few in
+// 10^8).
 //
 // Method: argument reduction, then a polynomial whose coefficients are the
 // minimax ones of the stated function on the stated interval (computed by
