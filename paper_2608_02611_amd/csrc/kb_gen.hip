@@ -126,16 +126,9 @@ hipError_t launch_typed(void* dst, uint64_t n, float p0, float p1, uint64_t seed
     return hipGetLastError();
 }
 
-// Student-t with 3 degrees of freedom of one block's words: the ratio of the
-// first binary64 normal to the root of the other three's mean square (a
-// chi-square over its degrees of freedom), rounded once to binary32.
-__device__ __forceinline__ float student_t3(u32x4 w) {
-    double z0, z1, z2, z3;
-    box_muller64<DeviceSeed>(w.x, w.y, z0, z1);
-    box_muller64<DeviceSeed>(w.z, w.w, z2, z3);
-    const double chi2 = (z1 * z1 + z2 * z2) + z3 * z3;
-    return (float)(z0 / sqrt(chi2 / 3.0));
-}
+// Student-t with 3 degrees of freedom of one block's words, rounded once to
+// binary32.
+__device__ __forceinline__ float student_t3(u32x4 w) { return (float)student_t3_64<DeviceSeed>(w.x, w.y, w.z); }
 
 // An arithmetic result rounded to the storage type (nearest even); a NaN
 // result is stored as the type's positive quiet NaN, whatever NaN the

@@ -125,4 +125,28 @@ KB_MATH void box_muller64(uint32_t xa, uint32_t xb, double& zc, double& zs) {
     zs = rho * s;
 }
 
+// Student-t with 3 degrees of freedom of one block's words x, y, z (, w): the
+// ratio of the first normal to the root of the other three's mean square (a
+// chi-square over its degrees of freedom).  With T1, T2 = -2 ln u of the two
+// pairs and theta the angle of the first,
+//   z0 = sqrt(T1) cos theta, z1^2 = T1 sin^2 theta, z2^2 + z3^2 = T2
+// (sin^2 + cos^2 = 1: the second pair's angle drops out), so
+//   t = cos theta sqrt(3 T1 / D), D = T1 sin^2 theta + T2
+//     = cos theta A rsqrt(A D),   A = 3 T1:
+// one sine and cosine, one inverse root and no quotient, where the definition
+// read literally takes two, three and one.  Bound by instruction issue: 16.8
+// million fp32 elements 87 us, 121 us taken literally.
+template <class Seed>
+KB_MATH double student_t3_64(uint32_t x, uint32_t y, uint32_t z) {
+    const double T1 = neg2_log_u01<Seed>(x), T2 = neg2_log_u01<Seed>(z);
+    double s, c;
+    sincos_2pi_u(y, s, c);
+    const double A = 3.0 * T1, D = math_fma(T1 * s, s, T2);
+    // A = 0 gives 0 (the floor keeps the inverse root finite); D = 0 (u = 1
+    // in the second pair and z1 = 0) gives the quotient by zero
+    double r = math_rsqrt<Seed>(__builtin_fmax(A * D, 0x1p-1000));
+    r = D == 0.0 ? __builtin_inf() : r;
+    return c * (A * r);
+}
+
 }  // namespace kb

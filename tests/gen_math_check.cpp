@@ -41,7 +41,7 @@ struct Worst {
 template <int SIGN>
 void check(const std::vector<uint32_t>& words) {
     using S = Seed<SIGN>;
-    Worst lg, root, sn, cs;
+    Worst lg, root, sn, cs, t3;
     for (uint32_t x : words) {
         const double t = kb::neg2_log_u01<S>(x);
         // (log1p keeps the accuracy of the oracle value itself near u = 1)
@@ -55,6 +55,27 @@ void check(const std::vector<uint32_t>& words) {
         sn.see(ulps(s, sinl((long double)theta)), x);
         cs.see(ulps(c, cosl((long double)theta)), x);
     }
+    // Student-t: words three apart in the list, against the definition with
+    // all four normals (any second angle)
+    auto log2u = [](uint32_t x) {
+        const long double m = (long double)x + 1.0L;
+        return -2.0L * (x > 0xF0000000u ? log1pl((m - 0x1p32L) * 0x1p-32L) : logl(m * 0x1p-32L));
+    };
+    auto literal = [&](uint32_t x, uint32_t y, uint32_t z, uint32_t w) {
+        const long double th = 6.283185307179586476925286766559 * ((double)y * 0x1p-32), ph = (long double)w * 1e-9L;
+        const long double r1 = sqrtl(log2u(x)), r2 = sqrtl(log2u(z));
+        const long double z1 = r1 * sinl(th), z2 = r2 * cosl(ph), z3 = r2 * sinl(ph);
+        return r1 * cosl(th) / sqrtl((z1 * z1 + z2 * z2 + z3 * z3) / 3.0L);
+    };
+    for (size_t i = 0; i + 3 < words.size(); ++i) {
+        const uint32_t x = words[i], y = words[i + 1], z = words[i + 2], w = words[i + 3];
+        t3.see(ulps(kb::student_t3_64<S>(x, y, z), literal(x, y, z, w)), x);
+    }
+    // u = 1 in the first pair: zero; in the second with z1 = 0: a quotient by zero
+    const uint32_t one = 0xFFFFFFFFu;
+    const bool edges = kb::student_t3_64<S>(one, 77u, 5u) == 0.0 && std::isinf(kb::student_t3_64<S>(5u, 0u, one)) &&
+                       std::isnan(kb::student_t3_64<S>(one, 0u, one));
+    std::printf("edges %d 0\nstudent_t3 %.3f %08x\n", edges ? 0 : 1, t3.u, t3.at);
     std::printf("neg2_log %.3f %08x\nsqrt %.3f %08x\nsin %.3f %08x\ncos %.3f %08x\n", lg.u, lg.at, root.u, root.at,
                 sn.u, sn.at, cs.u, cs.at);
 }
