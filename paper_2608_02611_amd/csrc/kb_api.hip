@@ -2,6 +2,7 @@
 // validation, the policy gate, launch planning and the statistics readback.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <chrono>
 #include <cmath>
@@ -180,11 +181,30 @@ int resident_blocks(int dtype, int kg, bool fail_fast = false, bool wide = false
         return 0;
     return cus * screen_blocks_per_cu(dtype, kg, fail_fast, wide, loc);
 }
-int plan_group_size(int n_cands, int dtype) {
-    // Measured on the five screening workloads: groups of 4 for fp32 and
-    // for short candidate lists, 8 for long lists of 16-bit tensors (the
-    // reference is then re-read by fewer groups).
+int plan_group_size(int n_cands, uint64_t numel, int dtype, bool fail_fast) {
+    if (n_cands < 1) return 1;  // (no plan; the caller reports it)
+    // Long passes, measured on the five screening workloads: groups of 4 for
+    // fp32 and for short candidate lists, 8 for long lists of 16-bit tensors
+    // (the reference is then re-read by fewer groups).
     int kg_cap = (dtype != DT_F32 && n_cands >= 32) ? 8 : 4;
+    // Short passes are bound by latency, not bandwidth: each wave visits a
+    // few chunks at most, so the time is that of the kernel's code run about
+    // once -- the chain through all candidates of the group and the fetch of
+    // instructions that nothing has brought in yet -- and a kernel of 4 or 8
+    // candidates has that many times the code.  Below the stated bytes of all
+    // candidates, groups of 1 or 2 (us; groups of 4 or 8 -> 2 -> 1):
+    //   4 x 65536 fp32 12.4 -> 9.2 -> 7.8; 64 x 65536 fp16 20.4 -> 11.8 -> 10.3;
+    //   16 x 262016 fp32 (16 MiB) 19.7 -> 14.7 -> 11.9;
+    //   64 x 131072 fp32 (32 MiB) 15.9 -> 13.9 -> 17.1;
+    //   16 x 2^20 fp32 (64 MiB) 19.4 -> 17.9 -> 19.1;
+    //   64 x 2^20 fp16 (128 MiB) 34.7 -> 35.7 -> 52.7;
+    // fail-fast, whose rounds hold few groups: 64 x 65536 fp16 20.7 -> 11.9 ->
+    //   11.1; 16 x 2^19 fp16 (16 MiB) 16.3 -> 15.1 -> 18.8; 16 x 2^20 fp16
+    //   (32 MiB) 20.1 -> 25.5 -> 29.1.
+    const uint64_t limit1 = fail_fast ? 8u << 20 : 16u << 20, limit2 = fail_fast ? 16u << 20 : 64u << 20;
+    const uint64_t one = (uint64_t)n_cands * elem_size(dtype);  // bytes of one element of every candidate
+    if (numel <= limit1 / one) kg_cap = 1;
+    else if (numel <= limit2 / one) kg_cap = 2;
     if (tuning().kg_cap > 0) kg_cap = tuning().kg_cap;
     int kg = 1;
     while (kg < n_cands && kg < kg_cap) kg *= 2;
@@ -202,10 +222,15 @@ bool make_plan(int n_cands, int n_acc, uint64_t numel, int dtype, int resident_b
     P.numel = numel;
     const uint64_t vec = 16 / elem_size(dtype);
     P.n_vec = numel / vec;
-    // Candidates per group: all of them when few, else 8 (chosen from n_cands
-    // so that the workspace sized for n_cands always suffices).
-    P.kg = plan_group_size(n_cands, dtype);
-    const int groups_max = (n_cands + P.kg - 1) / P.kg;
+    // Candidates per group (chosen from n_cands so that the workspace sized
+    // for n_cands always suffices).  The plain and the fail-fast launch may
+    // group differently; the workspace is laid out for both.
+    P.kg = plan_group_size(n_cands, numel, dtype, serial_groups);
+    const int kg_plain = plan_group_size(n_cands, numel, dtype, false);
+    const int kg_ff = plan_group_size(n_cands, numel, dtype, true);
+    const int groups_plain = (n_cands + kg_plain - 1) / kg_plain, groups_ff = (n_cands + kg_ff - 1) / kg_ff;
+    const int groups_max = std::max(groups_plain, groups_ff);
+    const int slots_max = std::max(groups_plain * kg_plain, groups_ff * kg_ff);
     P.n_groups = n_acc > 0 ? (n_acc + P.kg - 1) / P.kg : 0;
     // Work-groups per candidate group (stripes; a multiple of 8, the XCD count):
     //  - at least enough that one work-group sees fewer than 2^31 elements
@@ -233,7 +258,7 @@ bool make_plan(int n_cands, int n_acc, uint64_t numel, int dtype, int resident_b
         if (c < 8) c = 8;
         return c;
     };
-    const uint64_t c_plain = clamp_c(align_up((4096 + groups_max - 1) / groups_max, 8));
+    const uint64_t c_plain = clamp_c(align_up((4096 + groups_plain - 1) / groups_plain, 8));
     const uint64_t c_ws = clamp_c(c_plain > 2048 ? c_plain : 2048);
     if (c_ws > (1u << 20)) return false;
     int blocks_total = tuning().blocks_total;
@@ -265,7 +290,7 @@ bool make_plan(int n_cands, int n_acc, uint64_t numel, int dtype, int resident_b
     off += (size_t)groups_max * super_ws * 8;
     off = align_up(off, 256);
     P.off_ff_flags = off;
-    off = align_up(off + (size_t)groups_max * P.kg * (size_t)(1 + super_ws) * 128, 256);
+    off = align_up(off + (size_t)slots_max * (size_t)(1 + super_ws) * 128, 256);
     P.off_part_u32 = off;
     off = align_up(off + (size_t)kPartPlanes * n_cands * Cw * 4, 256);
     P.off_part_ssd = off;
@@ -326,7 +351,7 @@ int screen_with_status(const char* who, const kb_tensor* ref, const kb_tensor* c
     for (int k = 0; k < n_cands; ++k) n_acc += status[k] == KB_STATUS_OK;
 
     ScreenPlan P;
-    const int kg = plan_group_size(n_cands, dtype);
+    const int kg = plan_group_size(n_cands, numel, dtype, fail_fast);
     const bool wide = use_wide_kernel(dtype, kg, fail_fast, numel, loc);
     if (!make_plan(n_cands, n_acc, numel, dtype, resident_blocks(dtype, kg, fail_fast, wide, loc), fail_fast, &P))
         return fail(KB_ERR_INVALID_ARG, "%s: no launch plan (numel=%llu)", who,
@@ -447,7 +472,7 @@ int kb_screen_launch(int n_cands, uint64_t numel, int dtype, kb_launch* out) {
     if (out == nullptr) return fail(KB_ERR_INVALID_ARG, "kb_screen_launch: out is NULL");
     if (!is_float_dtype(dtype)) return fail(KB_ERR_DTYPE, "dtype %d not screenable", dtype);
     ScreenPlan P;
-    const int kg = plan_group_size(n_cands, dtype);
+    const int kg = plan_group_size(n_cands, numel, dtype, false);
     if (!make_plan(n_cands, n_cands, numel, dtype,
                    resident_blocks(dtype, kg, false, use_wide_kernel(dtype, kg, false, numel)), false, &P))
         return fail(KB_ERR_INVALID_ARG, "no launch plan for n_cands=%d numel=%llu", n_cands,

@@ -81,8 +81,8 @@ struct Part2 {
 bool make_plan(int n_cands, int n_acc, uint64_t numel, int dtype, int resident_blocks,
                bool serial_groups, ScreenPlan* plan);
 
-// Candidates per group the plan picks for n_cands candidates.
-int plan_group_size(int n_cands, int dtype);
+// Candidates per group the plan picks for n_cands candidates of numel elements.
+int plan_group_size(int n_cands, uint64_t numel, int dtype, bool fail_fast);
 
 // Whether a plain launch takes the screening kernel built for 5 waves per
 // SIMD (fp32, 4 candidates per group, at least 2^22 elements).  fp32 at 4
