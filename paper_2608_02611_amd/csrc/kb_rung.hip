@@ -7,12 +7,14 @@
 // over the baseline (Appendix A.5), the quantiles behind the tail ratios of
 // Table A.3, and per candidate the latency and the runtime score of Eq. 2.
 //
-// rows_wave_kernel   rows of at most 64 samples (every rung of the paper):
-//                    one wave per row, one sample per lane, a bitonic sort
-//                    across the lanes;
-// rows_block_kernel  longer rows (up to kRungMaxIter): one work-group per
-//                    row, bitonic sort in LDS;
-// scores_kernel      one thread per candidate: latency, score, speedups;
+// rung_kernel        rows of at most 256 samples (every rung of the paper) on
+//                    at most 64 shapes: one work-group per candidate, one
+//                    wave per row, up to 4 samples per lane, a bitonic sort
+//                    across lanes and registers, then the candidate's score;
+// rows_block_kernel  longer rows (up to kRungMaxIter) or more shapes: one
+//                    work-group per row, bitonic sort in LDS;
+// scores_kernel      after those, one thread per candidate: latency, score,
+//                    speedups;
 // promote_kernel     the promotion decision over the scores.
 //
 // Every sum runs left to right in binary64, as the definitions read (the
@@ -65,49 +67,189 @@ __device__ __forceinline__ void write_row(kb_sample_stats* o, int n, bool valid,
     *o = r;
 }
 
-__device__ __forceinline__ double readlane_f64(double v, int l) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, l);
-    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), l);
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+// The 64-bit value of lane ^ M: one DPP permutation inside a row of 16 lanes
+// (two for M = 4), a bpermute across rows.
+template <int M>
+__device__ __forceinline__ uint64_t lane_xor(uint64_t v) {
+    if constexpr (M == 1) return dpp_u64<DPP_QUAD_XOR1>(v);
+    else if constexpr (M == 2) return dpp_u64<DPP_QUAD_XOR2>(v);
+    else if constexpr (M == 3) return dpp_u64<0x1B>(v);  // quad_perm [3, 2, 1, 0]
+    else if constexpr (M == 7) return dpp_u64<DPP_ROW_HALF_MIRROR>(v);
+    else if constexpr (M == 15) return dpp_u64<DPP_ROW_MIRROR>(v);
+    else if constexpr (M == 4) return lane_xor<3>(lane_xor<7>(v));
+    else if constexpr (M == 8) return dpp_u64<0x128>(v);  // row_ror:8
+    else return __shfl_xor((unsigned long long)v, M, 64);
 }
 
-// One wave per row: lane l holds sample l (+inf past the end), a bitonic
-// network over the lane index sorts ascending, and the quantiles read the
-// sorted values from their lanes.
-__global__ __launch_bounds__(kThreads) void rows_wave_kernel(const double* __restrict__ samples,
-                                                              int n_rows, int n,
-                                                              kb_sample_stats* __restrict__ rows) {
-    const int lane = threadIdx.x & 63;
-    const int row = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
-    if (row >= n_rows) return;  // whole waves
-    const double* t = samples + (size_t)row * (size_t)n;
-    double v = lane < n ? t[lane] : __builtin_inf();
-    const bool valid = __builtin_amdgcn_ballot_w64(lane < n && !sample_ok(v)) == 0;
-    // the mean's sum, left to right over the samples
-    double sum = 0.0;
-    if (valid) {
-        for (int i = 0; i < n; ++i) sum = __dadd_rn(sum, readlane_f64(v, i));
+// v[e] at lane l is element 64 e + l.  One step of the network: each element
+// meets its partner i ^ M and keeps the smaller of the two if its own bit H
+// (the top bit of M) is clear.
+template <int E, int M, int H>
+__device__ __forceinline__ void sort_step(uint64_t v[E], int lane) {
+    constexpr int ML = M & 63, ME = M >> 6;
+    uint64_t o[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const uint64_t x = v[e ^ ME];
+        if constexpr (ML != 0) o[e] = lane_xor<ML>(x);
+        else o[e] = x;
     }
-    double q50 = 0.0, q90 = 0.0, q95 = 0.0, q99 = 0.0;
-    if (valid) {
 #pragma unroll
-        for (int k = 2; k <= 64; k <<= 1) {
+    for (int e = 0; e < E; ++e) {
+        const bool upper = H < 64 ? (lane & H) != 0 : ((64 * e) & H) != 0;
+        v[e] = (o[e] < v[e]) != upper ? o[e] : v[e];  // (equal elements are the same bits)
+    }
+}
+
+template <int E, int J>
+__device__ __forceinline__ void sort_halve(uint64_t v[E], int lane) {
+    if constexpr (J > 0) {
+        sort_step<E, J, J>(v, lane);
+        sort_halve<E, J / 2>(v, lane);
+    }
+}
+
+// Bitonic sort, ascending, of 64 E non-negative binary64 values as bit
+// patterns (which order like the values): runs of K / 2 merge by a first step
+// against the mirrored partner i ^ (K - 1), then half-cleaners, so every
+// comparison points the same way.
+template <int E, int K = 2>
+__device__ __forceinline__ void wave_sort(uint64_t v[E], int lane) {
+    sort_step<E, K - 1, K / 2>(v, lane);
+    sort_halve<E, K / 4>(v, lane);
+    if constexpr (K < 64 * E) wave_sort<E, 2 * K>(v, lane);
+}
+
+// A row held by a wave: sample 64 e + lane in v[e], positive infinity past
+// the end; whether all n samples are valid.
+template <int E>
+__device__ __forceinline__ bool load_row(const double* t, int n, int lane, double v[E]) {
+    bool bad = false;
 #pragma unroll
-            for (int j = k >> 1; j > 0; j >>= 1) {
-                const double o = __shfl_xor(v, j, 64);
-                const bool lower = (lane & j) == 0;
-                const bool ascending = (lane & k) == 0;
-                v = (lower == ascending) ? fmin(v, o) : fmax(v, o);
+    for (int e = 0; e < E; ++e) {
+        const int i = 64 * e + lane;
+        v[e] = i < n ? t[i] : __builtin_inf();
+        bad |= i < n && !sample_ok(v[e]);
+    }
+    return __builtin_amdgcn_ballot_w64(bad) == 0;
+}
+
+// Sums of two rows, each left to right over its samples (two independent
+// chains, so the second costs no time).  The loop runs to a multiple of 4:
+// adding zero leaves a positive sum as it is.
+template <int E>
+__device__ __forceinline__ void row_sums(const double a[E], const double b[E], int n, int lane, double& sa, double& sb) {
+    sa = 0.0;
+    sb = 0.0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const bool in = 64 * e + lane < n;
+        const double x = in ? a[e] : 0.0, y = in ? b[e] : 0.0;
+        const int m = min(64, n - 64 * e);
+        for (int i = 0; i < m; i += 4) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                sa = __dadd_rn(sa, readlane_f64(x, i + u));
+                sb = __dadd_rn(sb, readlane_f64(y, i + u));
             }
         }
-        auto x = [&](int i) { return readlane_f64(v, i); };
-        q50 = quantile(x, n, 0.5);
-        q90 = quantile(x, n, 0.9);
-        q95 = quantile(x, n, 0.95);
-        q99 = quantile(x, n, 0.99);
     }
-    if (lane == 0) write_row(&rows[row], n, valid, sum, q50, q90, q95, q99);
+}
+
+// Rows of at most 64 E samples on at most kFusedShapes shapes: one work-group
+// per candidate, one wave per row (striding over the shapes), then the
+// candidate's score.  The wave also sums the baseline's row of its shape, so
+// the speedups and the score need nothing from another work-group and the
+// whole of kb_rung_stats is one launch.  The kernel is a chain of latencies
+// (a few thousand waves of some 500 instructions): the sort's steps are DPP
+// permutations instead of LDS permutes where they stay inside 16 lanes, and
+// the quantiles, the quotients and the stores of a row are one each, spread
+// over the lanes.
+// 1024 candidates x 3 shapes x 60 samples: rows and scores apart 7.4 + 6.2 us
+// and a launch, this kernel 9.5 us; the promotion's batched loads 8.5 -> 5.9.
+constexpr int kFusedShapes = 64;
+constexpr int kWaveSamples = 4;  // samples per lane at most
+
+template <int E>
+__global__ __launch_bounds__(kThreads) void rung_kernel(RungParams p, const double* __restrict__ samples,
+                                                        kb_sample_stats* __restrict__ rows,
+                                                        kb_rung_score* __restrict__ scores) {
+    __shared__ double s_mean[2][kFusedShapes];  // own, baseline
+    __shared__ int s_valid[2][kFusedShapes];
+    const int lane = threadIdx.x & 63;
+    const int n = p.n_iter, S = p.n_shapes, c = blockIdx.x;
+    const double nan = __builtin_nan("");
+    for (int s = threadIdx.x >> 6; s < S; s += blockDim.x >> 6) {
+        const size_t row = (size_t)c * S + s;
+        double v[E], b[E];
+        const bool valid = load_row<E>(samples + row * (size_t)n, n, lane, v);
+        // (no baseline: its own row again, not used)
+        const size_t base_row = p.base >= 0 ? (size_t)p.base * S + s : row;
+        const bool base_valid = load_row<E>(samples + base_row * (size_t)n, n, lane, b) && p.base >= 0;
+        double sum, base_sum;
+        row_sums<E>(v, b, n, lane, sum, base_sum);
+        uint64_t x[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) x[e] = __builtin_bit_cast(uint64_t, v[e]);
+        wave_sort<E>(x, lane);
+        // Lane w forms word w of the record: the mean (0), the quantiles
+        // (1-4), their ratios to the median (5-7), the speedup (8; first the
+        // baseline's mean).  The p-quantile of the sorted samples: linear
+        // interpolation between the order statistics around h = (n - 1) p.
+        const double q_p = lane == 1 ? 0.5 : lane == 2 || lane == 5 ? 0.9 : lane == 3 || lane == 6 ? 0.95 : 0.99;
+        const double h = __dmul_rn((double)(n - 1), q_p);
+        const int k = (int)floor(h);
+        const int ka = min(k, n - 1), kb = min(k + 1, n - 1);
+        uint64_t xa = __shfl((unsigned long long)x[0], ka & 63, 64), xb = __shfl((unsigned long long)x[0], kb & 63, 64);
+#pragma unroll
+        for (int e = 1; e < E; ++e) {
+            const uint64_t ya = __shfl((unsigned long long)x[e], ka & 63, 64);
+            const uint64_t yb = __shfl((unsigned long long)x[e], kb & 63, 64);
+            if (ka >> 6 == e) xa = ya;
+            if (kb >> 6 == e) xb = yb;
+        }
+        const double fa = __builtin_bit_cast(double, xa), fb = __builtin_bit_cast(double, xb);
+        double q = fa;
+        if (k < n - 1) q = __dadd_rn(fa, __dmul_rn(__dsub_rn(h, (double)k), __dsub_rn(fb, fa)));
+        const double q50 = readlane_f64(q, 1);
+        const double num = lane == 0 ? sum : lane == 8 ? base_sum : q;
+        const double quot = num / (lane == 0 || lane == 8 ? (double)n : q50);
+        const double mean = readlane_f64(quot, 0);
+        const double base_mean = base_valid ? readlane_f64(quot, 8) : nan;
+        double word = lane >= 1 && lane <= 4 ? q : quot;
+        if (lane == 8) word = base_mean / mean;
+        if (!valid) word = nan;
+        if (lane == 9)
+            word = __builtin_bit_cast(double, ((uint64_t)(valid ? 1u : 0u) << 32) | (uint32_t)n);
+        if (lane < 10) ((double*)&rows[row])[lane] = word;
+        if (lane == 0) {
+            s_mean[0][s] = valid ? mean : nan;
+            s_valid[0][s] = valid ? 1 : 0;
+            s_mean[1][s] = base_mean;
+            s_valid[1][s] = base_valid ? 1 : 0;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    // lane 0: the candidate, lane 1: the baseline.  Latency: the mean of the
+    // row means, left to right; NaN if a row is invalid.
+    const int who = lane & 1;
+    double lat = 0.0;
+    int ok = 1;
+    for (int s = 0; s < S; ++s) {
+        lat = __dadd_rn(lat, s_mean[who][s]);
+        ok &= s_valid[who][s];
+    }
+    lat = ok ? lat / (double)S : nan;
+    const bool own_ok = __builtin_amdgcn_readlane(ok, 0) != 0;
+    const double own = readlane_f64(lat, 0), base = readlane_f64(lat, 1);
+    // word 1: Eq. 2, the latency term plus the one rung term gamma(r) = alpha r + beta b_r; word 2: the speedup
+    double word = (lane == 1 ? 1e6 : base) / (lane == 1 ? (own > 1.0 ? own : 1.0) : own);
+    if (lane == 1) word = __dadd_rn(word, __dadd_rn(__dmul_rn(p.alpha, (double)p.rung), __dmul_rn(p.beta, p.budget)));
+    if (!own_ok) word = lane == 1 ? -__builtin_inf() : nan;
+    if (lane == 0) word = own;
+    if (lane == 3) word = __builtin_bit_cast(double, (uint64_t)(own_ok ? 1u : 0u));
+    if (lane < 4) ((double*)&scores[c])[lane] = word;
 }
 
 // One work-group per row of up to kRungMaxIter samples, sorted in LDS.
@@ -242,14 +384,29 @@ __global__ __launch_bounds__(kThreads) void promote_kernel(const kb_rung_score* 
     const double ki = rank_key(scores[i]);
     const bool valid_i = scores[i].valid != 0;
     int before = 0, before_elig = 0, n_elig = 0;
-    for (int j = lane; j < n; j += 64) {
-        const kb_rung_score sj = scores[j];
-        const double kj = rank_key(sj);
-        const bool elig = sj.valid != 0 && j != base;
-        const bool b = kj > ki || (kj == ki && j < i);
-        before += b;
-        before_elig += b && elig;
-        n_elig += elig;
+    // (kBatch scores per lane in flight: one after another, the loads'
+    // latencies were most of the kernel)
+    constexpr int kBatch = 8;
+    for (int j0 = lane; j0 < n; j0 += 64 * kBatch) {
+        double kj[kBatch];
+        int vj[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const kb_rung_score& s = scores[min(j0 + 64 * u, n - 1)];
+            kj[u] = s.score;
+            vj[u] = s.valid;
+        }
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const int j = j0 + 64 * u;
+            const bool valid = vj[u] != 0;
+            const double key = valid && kj[u] == kj[u] ? kj[u] : -__builtin_inf();
+            const bool elig = valid && j != base && j < n;
+            const bool b = j < n && (key > ki || (key == ki && j < i));
+            before += b;
+            before_elig += b && elig;
+            n_elig += elig;
+        }
     }
     before = wave_sum_i32(before);
     before_elig = wave_sum_i32(before_elig);
@@ -277,16 +434,16 @@ hipError_t launch_rung_promote(const kb_rung_score* scores, int n, int base, int
 hipError_t launch_rung_stats(const RungParams& p, const double* samples, kb_sample_stats* rows,
                              kb_rung_score* scores, hipStream_t stream) {
     const int n_rows = p.n_cands * p.n_shapes;
-    if (p.n_iter <= 64) {
-        const int per_block = kThreads / 64;
-        hipLaunchKernelGGL(rows_wave_kernel, dim3((n_rows + per_block - 1) / per_block), dim3(kThreads),
-                           0, stream, samples, n_rows, p.n_iter, rows);
-    } else {
-        int P = 1;
-        while (P < p.n_iter) P <<= 1;
-        hipLaunchKernelGGL(rows_block_kernel, dim3(n_rows), dim3(kThreads), 0, stream, samples,
-                           p.n_iter, P, rows);
+    if (p.n_iter <= 64 * kWaveSamples && p.n_shapes <= kFusedShapes) {
+        const dim3 grid(p.n_cands), block(64 * (p.n_shapes < kThreads / 64 ? p.n_shapes : kThreads / 64));
+        if (p.n_iter <= 64) hipLaunchKernelGGL(rung_kernel<1>, grid, block, 0, stream, p, samples, rows, scores);
+        else if (p.n_iter <= 128) hipLaunchKernelGGL(rung_kernel<2>, grid, block, 0, stream, p, samples, rows, scores);
+        else hipLaunchKernelGGL(rung_kernel<4>, grid, block, 0, stream, p, samples, rows, scores);
+        return hipGetLastError();
     }
+    int P = 1;
+    while (P < p.n_iter) P <<= 1;
+    hipLaunchKernelGGL(rows_block_kernel, dim3(n_rows), dim3(kThreads), 0, stream, samples, p.n_iter, P, rows);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(scores_kernel, dim3((p.n_cands + kThreads - 1) / kThreads), dim3(kThreads), 0,

@@ -120,3 +120,18 @@ def test_alpha_beta_variants(dev):
     for alpha, beta, budget in ((0.0, 0.0, 0.0), (1.0, 0.5, 123.25), (-0.3, 2.0, 7.0)):
         check(t, dev, base=2, rung=3, budget=budget, alpha=alpha, beta=beta,
               label="alpha=%g beta=%g" % (alpha, beta))
+
+
+@pytest.mark.parametrize("n_iter", [1, 64, 65, 127, 129, 192, 255, 256, 257])
+@pytest.mark.parametrize("S", [1, 4, 5, 64, 65])
+def test_fused_kernel_edges(dev, n_iter, S):
+    """One launch per call up to 256 samples and 64 shapes, rows and scores
+    apart beyond; 1, 2 and 4 samples per lane, and shapes that the waves
+    stride over.  A baseline, none, and an invalid one (equal bits)."""
+    say("fused rung kernel", n_iter, S)
+    t = synth.timing_samples(3, S, n_iter, seed=40 + n_iter).numpy()
+    for base in (2, -1):
+        check(t, dev, base=base, rung=1, budget=16.0, label="n=%d S=%d base=%d" % (n_iter, S, base))
+    t[0, S - 1, n_iter - 1] = np.nan
+    for base in (0, 1):
+        check(t, dev, base=base, rung=1, budget=16.0, label="n=%d S=%d invalid, base=%d" % (n_iter, S, base))
