@@ -236,15 +236,20 @@ def _torch():
     return torch
 
 
+_dtype_codes = {}
+
+
 def dtype_code(t):
-    torch = _torch()
-    m = {torch.float32: KB_F32, torch.float16: KB_F16, torch.bfloat16: KB_BF16,
-         torch.int32: KB_U32}
-    if hasattr(torch, "uint32"):
-        m[torch.uint32] = KB_U32
-    if t.dtype not in m:
-        return -1
-    return m[t.dtype]
+    """KB_* code of a tensor's dtype, -1 if the library has none."""
+    global _dtype_codes
+    if not _dtype_codes:
+        torch = _torch()
+        m = {torch.float32: KB_F32, torch.float16: KB_F16, torch.bfloat16: KB_BF16,
+             torch.int32: KB_U32}
+        if hasattr(torch, "uint32"):
+            m[torch.uint32] = KB_U32
+        _dtype_codes = m
+    return _dtype_codes.get(t.dtype, -1)
 
 
 def describe(t, dtype=None):
@@ -267,9 +272,12 @@ def describe(t, dtype=None):
 
 
 def _stream_handle(stream=None):
+    if stream is not None:
+        return ctypes.c_void_p(stream.cuda_stream)
+    # the handle alone: torch.cuda.current_stream() also makes a Stream object,
+    # which took 2.7 us of a call's 8
     torch = _torch()
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
 # ------------------------------------------------------------- interface ---
@@ -532,9 +540,9 @@ def kb_rung_stats(samples, base=0, rung=0, budget=0.0, alpha=RUNG_ALPHA, beta=RU
     if scores is None:
         scores = torch.empty(max(1, C) * ctypes.sizeof(KbRungScore), dtype=torch.uint8,
                              device=samples.device)
-    _check(lib().kb_rung_stats(ctypes.c_void_p(samples.data_ptr()), C, S, N, int(base), int(rung),
+    _check(lib().kb_rung_stats(samples.data_ptr(), C, S, N, int(base), int(rung),
                                float(budget), float(alpha), float(beta),
-                               ctypes.c_void_p(rows.data_ptr()), ctypes.c_void_p(scores.data_ptr()),
+                               rows.data_ptr(), scores.data_ptr(),
                                _stream_handle(stream)))
     return rows, scores
 
@@ -569,10 +577,10 @@ def kb_rung_promote(scores, n_cands, base=0, frac_num=2, frac_den=5, stream=None
     rank = torch.empty(n_cands, dtype=torch.int32, device=dev)
     order = torch.empty(n_cands, dtype=torch.int32, device=dev)
     promoted = torch.empty(n_cands, dtype=torch.int32, device=dev)
-    _check(lib().kb_rung_promote(ctypes.c_void_p(scores.data_ptr()), int(n_cands), int(base),
-                                 int(frac_num), int(frac_den), ctypes.c_void_p(rank.data_ptr()),
-                                 ctypes.c_void_p(order.data_ptr()),
-                                 ctypes.c_void_p(promoted.data_ptr()), _stream_handle(stream)))
+    _check(lib().kb_rung_promote(scores.data_ptr(), int(n_cands), int(base),
+                                 int(frac_num), int(frac_den), rank.data_ptr(),
+                                 order.data_ptr(),
+                                 promoted.data_ptr(), _stream_handle(stream)))
     return rank, order, promoted
 
 
@@ -687,7 +695,7 @@ def kb_gen_inputs(dst, dist, p0=0.0, p1=1.0, seed=0, stream_id=0, sub=0, offset=
     """Fill torch tensor dst (contiguous) with elements offset.. of the seeded stream."""
     if not dst.is_contiguous():
         raise ValueError("dst must be contiguous")
-    _check(lib().kb_gen_inputs(ctypes.c_void_p(dst.data_ptr()), dtype_code(dst), dst.numel(),
+    _check(lib().kb_gen_inputs(dst.data_ptr(), dtype_code(dst), dst.numel(),
                                int(dist), float(p0), float(p1), int(seed), int(stream_id),
                                int(sub), int(offset), _stream_handle(stream)))
     return dst
@@ -697,7 +705,7 @@ def kb_gen_softmax_rows(dst, sigma, seed=0, stream_id=0, sub=0, stream=None):
     """Fill a contiguous float32 [rows, cols] tensor with softmax rows of NORMAL(0, sigma) logits."""
     if not dst.is_contiguous() or dst.dim() != 2:
         raise ValueError("dst must be a contiguous 2-d tensor")
-    _check(lib().kb_gen_softmax_rows(ctypes.c_void_p(dst.data_ptr()), dtype_code(dst), dst.shape[0],
+    _check(lib().kb_gen_softmax_rows(dst.data_ptr(), dtype_code(dst), dst.shape[0],
                                      dst.shape[1], float(sigma), int(seed), int(stream_id), int(sub),
                                      _stream_handle(stream)))
     return dst
@@ -708,7 +716,7 @@ def kb_gen_indices(m, n, device, seed=0, stream_id=0, sub=0, stream=None):
     holding the library's uint64 values (all below 2^63)."""
     torch = _torch()
     out = torch.empty(max(1, m), dtype=torch.int64, device=device)
-    _check(lib().kb_gen_indices(ctypes.c_void_p(out.data_ptr()), int(m), int(n), int(seed), int(stream_id),
+    _check(lib().kb_gen_indices(out.data_ptr(), int(m), int(n), int(seed), int(stream_id),
                                 int(sub), _stream_handle(stream)))
     return out[:m]
 
@@ -717,7 +725,7 @@ def kb_gen_perturb(dst, src, op, a=0.0, b=0.0, p=0.0, seed=0, stream_id=0, sub=0
     """dst = op(src) elementwise (contiguous tensors of one dtype; dst may be src)."""
     if not (dst.is_contiguous() and src.is_contiguous()) or dst.numel() != src.numel() or dst.dtype != src.dtype:
         raise ValueError("dst and src must be contiguous tensors of one size and dtype")
-    _check(lib().kb_gen_perturb(ctypes.c_void_p(dst.data_ptr()), ctypes.c_void_p(src.data_ptr()), dtype_code(dst),
+    _check(lib().kb_gen_perturb(dst.data_ptr(), src.data_ptr(), dtype_code(dst),
                                 dst.numel(), int(op), float(a), float(b), float(p), int(seed), int(stream_id),
                                 int(sub), int(offset), _stream_handle(stream)))
     return dst
@@ -730,8 +738,8 @@ def kb_gen_scatter(dst, ref, idx, mode, stream=None):
         raise ValueError("dst and ref must be contiguous tensors of one size and dtype")
     if idx.dtype != torch.int64 or not idx.is_contiguous():
         raise ValueError("idx must be a contiguous int64 tensor")
-    _check(lib().kb_gen_scatter(ctypes.c_void_p(dst.data_ptr()), ctypes.c_void_p(ref.data_ptr()), dtype_code(dst),
-                                dst.numel(), ctypes.c_void_p(idx.data_ptr()), idx.numel(), int(mode),
+    _check(lib().kb_gen_scatter(dst.data_ptr(), ref.data_ptr(), dtype_code(dst),
+                                dst.numel(), idx.data_ptr(), idx.numel(), int(mode),
                                 _stream_handle(stream)))
     return dst
 
