@@ -328,10 +328,11 @@ __device__ __forceinline__ void exact_chunk(const Raw<DT>& cand, const float r_i
 // ----------------------------------------------------------- positions ---
 // The position search inside the screening pass (LOC) keeps, per wave and
 // candidate: the first chunk whose count shows a mismatch (a wave visits its
-// chunks in increasing index order), searched for the element after the
-// loop; the chunk in which each lane's running max abs error last rose
-// (strictly, so its first occurrence), re-read after the loop; and the element
-// of the wave's own max rel error, found when it rises.  In the common path
+// chunks in increasing index order); the chunk in which each lane's running max abs error last rose
+// (strictly, so its first occurrence); and the element of the wave's own max
+// rel error, found when it rises.  Chunks are combined as the index of their
+// first element, and the finisher of the candidate group searches the two
+// that remain (write_positions).  In the common path
 // only the max-abs chunk costs instructions (a compare and two selects in
 // place of a max).
 constexpr uint64_t kNone = ~0ull;
@@ -457,6 +458,54 @@ __device__ __forceinline__ void report_dirty(const ScreenParams& p, const CandEn
     }
 }
 
+// A candidate's combined positions in the finisher, before the two chunks that
+// hold the first mismatch and the max abs error are searched: their starts
+// (below tfirst), or the elements themselves (in the tail); the element of the
+// max rel error; the max abs error's bits.
+struct Found {
+    uint64_t first_mismatch, max_abs, max_rel;
+    uint32_t max_abs_bits;
+};
+
+// Searches the chunks that `found` names and writes the positions, a wave per
+// candidate.  Called by the whole work-group, once per candidate group: every
+// wave of the grid used to search its own chunks after its loop, which read
+// four chunks per wave and candidate again, one after another: a fixed time
+// that medium sizes feel (100 x 2^18 fp32 47 -> 38 us, 64 x 2^19 fp32 33.8 ->
+// 31.7; 16 x 2^24 bf16 the same).
+template <int DT>
+__device__ __forceinline__ void write_positions(const ScreenParams& p, const CandEntry* table, int j0, int kg,
+                                                uint64_t tfirst, const Found* found) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t off = 16u * (uint32_t)lane;
+    const gbytes ref = uniform_ptr(p.ref);
+    __syncthreads();
+    for (int j = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); j < kg; j += kWaves) {
+        const CandEntry& entry = table[j0 + j];
+        const gbytes cand = uniform_ptr(entry.data);
+        uint64_t fm = found[j].first_mismatch, ma = found[j].max_abs;
+        const bool fm_chunk = fm < tfirst, ma_chunk = ma < tfirst;
+        if (fm_chunk || ma_chunk) {  // (so chunk 0 exists: read in the place of the other's)
+            constexpr uint64_t kBytes = chunk_bytes<DT>() / kChunk;
+            const uint64_t b0 = fm_chunk ? fm * kBytes : 0, b1 = ma_chunk ? ma * kBytes : 0;
+            const Raw<DT> c0 = load_chunk<DT, false>(uniform_ptr(cand + b0), off);
+            const Raw<DT> r0 = load_chunk<DT, false>(uniform_ptr(ref + b0), off);
+            const Raw<DT> c1 = load_chunk<DT, false>(uniform_ptr(cand + b1), off);
+            const Raw<DT> r1 = load_chunk<DT, false>(uniform_ptr(ref + b1), off);
+            if (fm_chunk) {
+                float rf[kE];
+#pragma unroll
+                for (int i = 0; i < kE; ++i) rf[i] = elem<DT>(r0, i);
+                fm += wave_min_u32(slot_offset<DT>(
+                    lane, lane_first_mismatch<DT>(c0, rf, p.atol, p.rtol, (p.flags & KB_EQUAL_NAN) != 0)));
+            }
+            if (ma_chunk)
+                ma += wave_min_u32(slot_offset<DT>(lane, lane_abs_slot<DT>(c1, r1, found[j].max_abs_bits)));
+        }
+        if (lane == 0) write_loc(&p.loc[entry.index], fm, ma, found[j].max_rel);
+    }
+}
+
 // Records (and, with positions, all -1 positions) of the rejected candidates
 // (written by group 0's finisher).
 __device__ __forceinline__ void write_rejected(const ScreenParams& p, const CandEntry* table) {
@@ -517,13 +566,13 @@ __device__ __forceinline__ void clear_ff_words(const ScreenParams& p, int j0, in
 //
 // LOC: the variant that also finds each candidate's positions (p.loc): the
 // first mismatching element and the first elements at which the max abs and
-// max rel errors are reached.  Per wave and candidate: the first mismatch is
-// searched, after the loop, in the first chunk whose count showed one (the
-// wave's chunks come in increasing index order, so later ones can only be
-// larger); each lane keeps the chunk in which its max abs error last rose
-// (strictly: the first chunk that holds its maximum), and after the loop the
-// lanes holding the wave's maximum re-read that chunk for the element; the
-// max-rel element is found in the chunk that raises the wave's own maximum.
+// max rel errors are reached.  Per wave and candidate: the first chunk whose
+// count showed a mismatch (the wave's chunks come in increasing index order,
+// so later ones can only be larger); each lane keeps the chunk in which its
+// max abs error last rose (strictly: the first chunk that holds its maximum);
+// the max-rel element is found in the chunk that raises the wave's own
+// maximum.  The group's finisher searches the first mismatch and the max abs
+// error in the one chunk each that remains.
 // The max-rel filter still uses the work-group's shared value, lowered by
 // one binary32 step so that elements tying it pass (see the fast path).  A
 // wave's own maximum then skips values below the shared one, but every
@@ -549,6 +598,7 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
     __shared__ double s_sr1c[FF ? KG : 1];  // single-level finish, per candidate
     __shared__ uint32_t s_told[FF ? KG : 1];  // fail-fast: the work-group knows candidate j failed
     __shared__ uint64_t s_idx[LOC ? kWaves : 1][LOC ? KG : 1][IX_COUNT];  // positions per wave
+    __shared__ Found s_found[LOC ? KG : 1];  // the finisher's combined positions
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -756,9 +806,9 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
                     publish_rel(&s_rel[j], o, lane);
                 }
                 if constexpr (LOC) {
-                    // the wave's first mismatching chunk (searched after the loop)
+                    // the wave's first mismatching chunk (searched at the end)
                     if (!((fm_found >> j) & 1u) && mism[j] != mism0) {
-                        set_idx(&s_idx[wave][j][IX_FIRST_MISMATCH], chunk, lane);
+                        set_idx(&s_idx[wave][j][IX_FIRST_MISMATCH], ebase, lane);
                         fm_found |= 1u << j;
                     }
                 }
@@ -767,7 +817,7 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
             mism[j] += (uint32_t)kChunk - nmatch;
             if constexpr (LOC) {
                 if (!((fm_found >> j) & 1u) && nmatch != (uint32_t)kChunk) {
-                    set_idx(&s_idx[wave][j][IX_FIRST_MISMATCH], chunk, lane);
+                    set_idx(&s_idx[wave][j][IX_FIRST_MISMATCH], ebase, lane);
                     fm_found |= 1u << j;
                 }
                 if (__float_as_uint(tmax) > amax[j]) {
@@ -863,9 +913,6 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
     // elements 1..7 compare 0 with 0, which changes no statistic).
     uint32_t n_tail = 0u;  // tail elements this wave compared (for every live candidate)
     const uint64_t tfirst = n_chunks * kChunk;
-    // positions: candidates whose first mismatch was found in a chunk (the
-    // slot holds the chunk number until it is searched, below)
-    const uint32_t fm_chunked = fm_found;
     if (stripe == 0) {
         const uint64_t first = tfirst;
         for (uint64_t base = first; base < p.numel; base += kThreads) {
@@ -921,28 +968,6 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
         }
     }
 
-    // Positions: the first mismatch of each candidate whose first
-    // mismatching chunk of this wave is known, searched in that chunk.
-    if constexpr (LOC) {
-#pragma unroll
-        for (int j = 0; j < KG; ++j) {
-            if (j >= kg || !((fm_chunked >> j) & 1u)) continue;
-            const uint64_t c = ((uint64_t)__builtin_amdgcn_readfirstlane(
-                                   (uint32_t)(s_idx[wave][j][IX_FIRST_MISMATCH] >> 32))
-                               << 32) |
-                               __builtin_amdgcn_readfirstlane((uint32_t)s_idx[wave][j][IX_FIRST_MISMATCH]);
-            const uint64_t cb = c * chunk_bytes<DT>();
-            const Raw<DT> cv = load_chunk<DT, false>(uniform_ptr(cand[j] + cb), off);
-            const Raw<DT> rv = load_chunk<DT, false>(uniform_ptr(ref + cb), off);
-            float rf[kE];
-#pragma unroll
-            for (int i = 0; i < kE; ++i) rf[i] = elem<DT>(rv, i);
-            const uint32_t m =
-                wave_min_u32(slot_offset<DT>(lane, lane_first_mismatch<DT>(cv, rf, atol, rtol, equal_nan)));
-            set_idx(&s_idx[wave][j][IX_FIRST_MISMATCH], c * kChunk + m, lane);
-        }
-    }
-
     // Wave reductions, then the work-group's partials in wave order.
 #pragma unroll
     for (int j = 0; j < KG; ++j) {
@@ -950,28 +975,19 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
         const double sd = wave_sum_f64(s_ssd[j][threadIdx.x]);
         const uint32_t am = wave_max_u32(amax[j]);
         if constexpr (LOC) {
-            // the element of the wave's max abs error.  Every element of a
-            // chunk lies below every element of a later chunk (and the tail
-            // codes follow the chunks in index order), so the smallest index
-            // holding the maximum is in the earliest chunk in which a lane
-            // first reached it: only the lanes whose first occurrence is in
-            // that chunk re-read it -- one chunk, coalesced, however many
-            // lanes tie
+            // where the wave's max abs error is: the start of its chunk, or the
+            // element itself in the tail.  Every element of a chunk lies below
+            // every element of a later chunk (and the tail codes follow the
+            // chunks in index order), so the smallest index holding the
+            // maximum is in the earliest chunk in which a lane first reached it
             uint64_t ai = kNone;
             if (am != 0u) {
                 const uint32_t ac = wave_min_u32(amax[j] == am ? achunk[j] : ~0u);
-                uint64_t mine = kNone;
-                if (amax[j] == am && achunk[j] == ac) {
-                    if (ac < n_chunks) {
-                        const uint64_t cb = (uint64_t)ac * chunk_bytes<DT>();
-                        const Raw<DT> c = load_chunk<DT, false>(uniform_ptr(cand[j] + cb), off);
-                        const Raw<DT> rr = load_chunk<DT, false>(uniform_ptr(ref + cb), off);
-                        mine = (uint64_t)ac * kChunk + slot_offset<DT>(lane, lane_abs_slot<DT>(c, rr, am));
-                    } else {
-                        mine = tfirst + (uint64_t)(ac - (uint32_t)n_chunks) * kThreads + threadIdx.x;
-                    }
-                }
-                ai = wave_min_u64(mine);
+                if (ac < n_chunks) ai = (uint64_t)ac * kChunk;
+                else
+                    ai = wave_min_u64(amax[j] == am && achunk[j] == ac
+                                          ? tfirst + (uint64_t)(ac - (uint32_t)n_chunks) * kThreads + threadIdx.x
+                                          : kNone);
             }
             if (lane == 0) s_idx[wave][j][IX_MAX_ABS] = ai;
         }
@@ -1177,8 +1193,9 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
                 else
                     write_record(&p.stats[table[j0 + jj].index], p.numel, mi, na, pi, ni, ma, mr, bd,
                                  sd, s_sr1);
-                if constexpr (LOC) write_loc(&p.loc[table[j0 + jj].index], i0, i1, i2);
+                if constexpr (LOC) s_found[jj] = Found{i0, i1, i2, ma};
             }
+            if constexpr (LOC) write_positions<DT>(p, table, j0, kg, tfirst, s_found);
             if (g == 0) write_rejected(p, table);
             if (threadIdx.x == 0) st_coherent(&p.tickets1[(size_t)g * S + m], (uint64_t)0);
             if constexpr (FF) clear_ff_words(p, j0, KG);
@@ -1274,7 +1291,7 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
             i0 = row_min_u64(i0);
             i1 = row_min_u64(ma_own == ma ? i1 : kNone);
             i2 = row_min_u64(mr_own == mr ? i2 : kNone);
-            if (sl == 0) write_loc(&p.loc[table[j0 + jj].index], i0, i1, i2);
+            if (sl == 0) s_found[jj] = Found{i0, i1, i2, ma};
         }
         if constexpr (FF) {
             nr = row_sum_u64(nr);
@@ -1287,6 +1304,7 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
                              sr);
         }
     }
+    if constexpr (LOC) write_positions<DT>(p, table, j0, kg, tfirst, s_found);
     // Group 0's finisher also writes the rejected candidates' records.
     if (g == 0) write_rejected(p, table);
     // Leave the ticket and the failed words at zero (every work-group of the
