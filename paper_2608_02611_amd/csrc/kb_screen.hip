@@ -260,21 +260,22 @@ struct NonFinite {
 };
 
 // The definition, element by element, for a whole lane chunk of one
-// candidate (every lane active).  Also the path for the ragged tail.
+// candidate (every lane active).  Also the path for the ragged tail, whose
+// lanes hold one element each (NE = 1).
 // Updates the wave's mismatch count, the lane's max abs error, the wave's
 // max-rel O and non-finite counts, and adds the lane's binary64 squared
 // differences to its LDS slot.  LOC: a rise of the lane's max abs error
 // also records `code` (the chunk) in achunk.
 // LOC also gives the lane's largest quotient in qm_out and its first slot in
 // qslot (kE if no quotient is positive).
-template <int DT, bool LOC>
-__device__ __forceinline__ void exact_chunk(const Raw<DT>& cand, const float r_in[kE], float atol,
+template <int DT, bool LOC, int NE = kE>
+__device__ __forceinline__ void exact_chunk(const Raw<DT>& cand, const float r_in[NE], float atol,
                                             float rtol, bool equal_nan, double* ssd_slot,
                                             uint32_t& mism, uint32_t& amax, uint32_t& achunk, uint32_t code,
                                             float& O, NonFinite& nf, float& qm_out, uint32_t& qslot) {
-    float r[kE];
+    float r[NE];
 #pragma unroll
-    for (int i = 0; i < kE; ++i) {
+    for (int i = 0; i < NE; ++i) {
         r[i] = r_in[i];
         opaque(r[i]);
     }
@@ -283,7 +284,7 @@ __device__ __forceinline__ void exact_chunk(const Raw<DT>& cand, const float r_i
     double sd = 0.0;
     qslot = kE;
 #pragma unroll
-    for (int i = 0; i < kE; ++i) {
+    for (int i = 0; i < NE; ++i) {
         const float c = elem<DT>(cand, i);
         const float ri = r[i];
         const bool cnan = __builtin_isnan(c);
@@ -349,12 +350,12 @@ __device__ __forceinline__ uint32_t slot_offset(int lane, uint32_t i) {
 
 // The lane's first slot whose element does not match (the definition's
 // predicate, special values included), kE if none.
-template <int DT>
-__device__ __forceinline__ uint32_t lane_first_mismatch(const Raw<DT>& cand, const float r[kE], float atol, float rtol,
+template <int DT, int NE = kE>
+__device__ __forceinline__ uint32_t lane_first_mismatch(const Raw<DT>& cand, const float r[NE], float atol, float rtol,
                                                         bool equal_nan) {
     uint32_t slot = kE;
 #pragma unroll
-    for (int i = kE - 1; i >= 0; --i) {
+    for (int i = NE - 1; i >= 0; --i) {
         const float c = elem<DT>(cand, i);
         const float d = fabsf(c - r[i]);
         const float tol = __builtin_isfinite(r[i]) ? __fadd_rn(atol, __fmul_rn(rtol, fabsf(r[i]))) : -1.0f;
@@ -681,16 +682,23 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
     // spread at the end is that of the last eighth only.  (Measured on the
     // 16 x 4096^2 bf16, 1024 x 256 x 1024 fp32, 64 x 8 x 2048 x 4096 fp16 and
     // 8 x 2^30 fp32 screens: 4.5%, 9%, 3.5% and 3.5% faster.)
-    const uint64_t n_mine = first < n_chunks ? (n_chunks - first + wstride - 1) / wstride : 0;
-    const uint64_t drop1 = n_mine / 2, drop2 = n_mine * 3 / 4, drop3 = n_mine * 7 / 8;
-    uint64_t n_seen = 0;
+    // (a work-group sees fewer than 2^31 elements: 32 bits hold the counts)
+    const uint32_t n_mine = first < n_chunks ? (uint32_t)((n_chunks - first + wstride - 1) / wstride) : 0u;
+    uint32_t left = n_mine, prio = 3u, drop = n_mine - n_mine / 2;
     if constexpr (!FF) __builtin_amdgcn_s_setprio(3);
     for (uint64_t chunk = first; chunk < n_chunks && (!FF || alive != 0u); chunk += wstride) {
         if constexpr (!FF) {
-            if (n_seen == drop1) __builtin_amdgcn_s_setprio(2);
-            if (n_seen == drop2) __builtin_amdgcn_s_setprio(1);
-            if (n_seen == drop3) __builtin_amdgcn_s_setprio(0);
-            ++n_seen;
+            if (left == drop) {
+                // (a jump over as many steps as fall on this chunk)
+                while (prio != 0u && left == drop) {
+                    --prio;
+                    drop = prio == 2u ? n_mine - n_mine * 3ull / 4 : n_mine - n_mine * 7ull / 8;
+                }
+                if (prio == 2u) __builtin_amdgcn_s_setprio(2);
+                else if (prio == 1u) __builtin_amdgcn_s_setprio(1);
+                else __builtin_amdgcn_s_setprio(0);
+            }
+            --left;
         }
         const uint64_t cb = chunk * chunk_bytes<DT>();
         // Re-materialise the lane offset inside the loop so that instruction
@@ -735,7 +743,7 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
         double rrd = (double)rr;
         // not in [2^-100, inf), NaN included, as one unsigned compare
         const bool rbad = __float_as_uint(rr) - 0x0D800000u >= 0x7F800000u - 0x0D800000u;
-        if (ballot(rbad)) {
+        if (__builtin_expect(ballot(rbad) != 0, 0)) {
             if (rbad) {
                 double t = 0.0;
 #pragma unroll
@@ -790,7 +798,7 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
             float ymax = y[0];
 #pragma unroll
             for (int i = 1; i < kE; ++i) ymax = fmaxf(ymax, y[i]);
-            if (ballot(!(acc < __builtin_inff()))) {
+            if (__builtin_expect(ballot(!(acc < __builtin_inff())) != 0, 0)) {
                 // NaN, infinity or a squared difference beyond binary32
                 float o = Own;
                 const uint32_t mism0 = mism[j];
@@ -831,7 +839,7 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
             // squares would underflow, so square in binary64
             const bool tiny = (__float_as_uint(tmax) - 1u) < (__float_as_uint(kTiny) - 1u);
             double add = (double)acc;
-            if (ballot(tiny)) {
+            if (__builtin_expect(ballot(tiny) != 0, 0)) {
                 if (tiny) {
                     double t = 0.0;
 #pragma unroll
@@ -846,7 +854,7 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
             if constexpr (kGuard<DT>)
                 hz = fmaf(-O, amin_nz, (O > 0.f && floorf(O) != O) ? 0x1p-124f : -__builtin_inff());
             const bool rel = fmaxf(ymax, hz) > 0.f;
-            if (ballot(rel)) {
+            if (__builtin_expect(ballot(rel) != 0, 0)) {
                 float qm = 0.f;
                 uint32_t qs = kE;
                 if (kGuard<DT> && ballot(hz > 0.f)) {
@@ -909,8 +917,8 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
     if constexpr (!FF) __builtin_amdgcn_s_setprio(0);
 
     // Ragged tail: the last numel mod 512 elements, by stripe 0 of each
-    // group, one element per thread, exact path (out-of-range lanes and
-    // elements 1..7 compare 0 with 0, which changes no statistic).
+    // group, one element per thread, exact path (out-of-range lanes compare 0
+    // with 0, which changes no statistic).
     uint32_t n_tail = 0u;  // tail elements this wave compared (for every live candidate)
     const uint64_t tfirst = n_chunks * kChunk;
     if (stripe == 0) {
@@ -921,10 +929,7 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
             uint32_t rb = 0;
             if (valid) rb = DT == DT_F32 ? ((const uint32_t*)p.ref)[e] : ((const uint16_t*)p.ref)[e];
             if constexpr (FF) n_tail += popc(ballot(valid));
-            float r[kE];
-            r[0] = widen_bits<DT>(rb);
-#pragma unroll
-            for (int i = 1; i < kE; ++i) r[i] = 0.f;
+            const float r[1] = {widen_bits<DT>(rb)};
             if (__builtin_isfinite(r[0])) ssr = __builtin_fma((double)r[0], (double)r[0], ssr);
 #pragma unroll
             for (int j = 0; j < KG; ++j) {
@@ -948,7 +953,7 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
                 // chunk code of the tail is n_chunks + (base - first) / 256
                 float qm;
                 uint32_t qs;
-                exact_chunk<DT, LOC>(cr, r, atol, rtol, equal_nan, &s_ssd[j][threadIdx.x], mism[j],
+                exact_chunk<DT, LOC, 1>(cr, r, atol, rtol, equal_nan, &s_ssd[j][threadIdx.x], mism[j],
                                      amax[j], achunk[j], (uint32_t)(n_chunks + (base - first) / kThreads), o,
                                      s_nf[wave][j], qm, qs);
                 orel[j] = __float_as_uint(o);
@@ -957,7 +962,7 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
                     if (o > o0) set_idx(&s_idx[wave][j][IX_MAX_REL], wave_min_u64(qm == o ? e : kNone), lane);
                     if (!((fm_found >> j) & 1u) && mism[j] != mism0) {
                         set_idx(&s_idx[wave][j][IX_FIRST_MISMATCH],
-                                wave_min_u64(lane_first_mismatch<DT>(cr, r, atol, rtol, equal_nan) < (uint32_t)kE
+                                wave_min_u64(lane_first_mismatch<DT, 1>(cr, r, atol, rtol, equal_nan) < (uint32_t)kE
                                                  ? e
                                                  : kNone),
                                 lane);
