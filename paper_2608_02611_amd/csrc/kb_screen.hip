@@ -126,6 +126,27 @@ __device__ __forceinline__ float elem(const Raw<DT>& x, int i) {
     else return bf16_bits_to_f32(i & 1 ? (x.w[i >> 1] >> 16) : (x.w[i >> 1] & 0xFFFFu));
 }
 
+// Element i minus r in binary32, one rounding.  fp16: the widening and the
+// difference are one instruction (v_fma_mix_f32: c * 1 - r, exact up to the
+// same one rounding, zeros and special values included), where a conversion
+// and a subtraction issue for half as long again (the fail-fast screen of 64 x
+// 2^24 values 289 -> 277 us, the two-output attention screen 195 -> 192).
+template <int DT>
+__device__ __forceinline__ float elem_minus(const Raw<DT>& x, int i, float r) {
+    if constexpr (DT == DT_F16) {
+        float s;
+        if (i & 1)
+            asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,0] op_sel_hi:[1,0,0]"
+                : "=v"(s)
+                : "v"(x.w[i >> 1]), "v"(r));
+        else
+            asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel_hi:[1,0,0]" : "=v"(s) : "v"(x.w[i >> 1]), "v"(r));
+        return s;
+    } else {
+        return elem<DT>(x, i) - r;
+    }
+}
+
 __device__ __forceinline__ uint32_t popc(uint64_t m) { return (uint32_t)__builtin_popcountll(m); }
 
 // Number of lanes with |s| <= tol (a wave-uniform count).  The compare and
@@ -551,6 +572,17 @@ __device__ __forceinline__ void clear_ff_words(const ScreenParams& p, int j0, in
     for (int i = threadIdx.x; i < kgs * lines; i += kThreads) st_coherent(ff_word(p, j0 + i / lines, i % lines), 0u);
 }
 
+// The launch's parameters, read from the kernel argument segment (whose first
+// argument they are) where this is called: read at the start of the kernel and
+// kept, the finish's pointers and sizes take 40 scalar registers that the loop
+// over the chunks then keeps in vector lanes (two to seven spill moves per
+// candidate and chunk in the fp16 builds, none with the plain ones now).
+__device__ __forceinline__ const ScreenParams& late_params() {
+    auto args = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    return *(const ScreenParams*)args;
+}
+
 // One work-group's part of the screen: candidate group g, element stripe
 // `stripe`, then the finish of the group if this work-group is its last.
 //
@@ -789,7 +821,7 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
             float tmax = 0.f, acc = 0.f;
 #pragma unroll
             for (int i = 0; i < kE; ++i) {
-                s[i] = elem<DT>(cr, i) - r[i];
+                s[i] = elem_minus<DT>(cr, i, r[i]);
                 nmatch += count_within(s[i], tol[i]);
                 tmax = fmaxf(tmax, fabsf(s[i]));
                 acc = fmaf(s[i], s[i], acc);
@@ -915,6 +947,11 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
     }
 
     if constexpr (!FF) __builtin_amdgcn_s_setprio(0);
+
+    // The tail and the finish read the launch's parameters from the kernel arguments again
+    // (see late_params).
+    {
+    const ScreenParams& p = late_params();
 
     // Ragged tail: the last numel mod 512 elements, by stripe 0 of each
     // group, one element per thread, exact path (out-of-range lanes compare 0
@@ -1317,6 +1354,7 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
     // finds them clean even if its tag happens to equal this call's.
     if (threadIdx.x == 0) st_coherent(&p.tickets2[g], (uint64_t)0);
     if constexpr (FF) clear_ff_words(p, j0, KG);
+    }
 }
 
 // Work-group id -> (candidate group, stripe).  Ids are dealt round robin to
