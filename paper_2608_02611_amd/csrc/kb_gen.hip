@@ -9,6 +9,8 @@
 // multiple of 4 store with one 16-byte (fp32/u32) or 8-byte (fp16/bf16)
 // write.  The work is ALU-bound (ten 32x32->64 multiply rounds per block,
 // plus binary64 log/sqrt/sincos per normal pair).
+#include <algorithm>
+
 #include "kb_device.hpp"
 #include "kb_internal.hpp"
 #include "kb_math.hpp"
@@ -26,6 +28,14 @@ struct DeviceSeed {
     static __device__ __forceinline__ double frexp_mant(double x) { return __builtin_amdgcn_frexp_mant(x); }
     static __device__ __forceinline__ int frexp_exp(double x) { return __builtin_amdgcn_frexp_exp(x); }
     static __device__ __forceinline__ double ldexp(double x, int n) { return __builtin_ldexp(x, n); }
+    // saturating (2^32 gives 2^32 - 1), which a C++ conversion does not promise
+    static __device__ __forceinline__ uint32_t to_u32(float x) {
+        uint32_t u;
+        asm("v_cvt_u32_f32 %0, %1" : "=v"(u) : "v"(x));
+        return u;
+    }
+    static __device__ __forceinline__ float log2(float x) { return __builtin_amdgcn_logf(x); }
+    static __device__ __forceinline__ float sqrt32(float x) { return __builtin_amdgcn_sqrtf(x); }
 };
 
 // Box-Muller on one word pair, each branch rounded once to binary32.
@@ -112,6 +122,108 @@ __global__ __launch_bounds__(256) void gen_kernel(void* __restrict__ dst, uint64
     }
 }
 
+// Normals stored in 16 bits.  The values are defined by the binary64 transform
+// rounded to binary32, scaled, and rounded again to 16 bits; only one in some
+// hundred of them lies close enough to a rounding boundary for more than 20
+// bits of the normal to matter.  So each normal is first formed in binary32
+// (rho32 and sincos32: the binary32 steps issue no faster than binary64's
+// here, but a pair takes 40 of them instead of 75) as an interval.  The errors
+// are relative -- rho 2^-22.6, the sine or cosine 2^-22.3, their product and
+// the definition's own rounding to binary32 2^-24 each, 2^-21.0 in all -- so
+// the binary32 normal lies between z (1 - e) and z (1 + e), e = 1.25 * 2^-21
+// (the two products' rounding included), and since the scaling and the
+// rounding are monotone, an interval whose two ends are stored as the same
+// bits stores the value's bits.  A
+// block with any other interval is put on the work-group's list and computed
+// by the binary64 path after the loop, when the list fills whole waves: the
+// outputs are the same bits as without the first pass.  Bound by instruction
+// issue: 3 x 33.5 million fp16 values 157 -> 105 us.
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// Two binary32 values (no NaN) rounded to storage, packed.
+template <int DT>
+__device__ __forceinline__ uint32_t pack16(float a, float b) {
+    asm volatile("" : "+v"(a), "+v"(b));  // (see to_f16_bits)
+    if constexpr (DT == DT_F16) return __builtin_bit_cast(uint32_t, f16x2{(_Float16)a, (_Float16)b});
+    else return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b});
+}
+
+// The stored bits of a word pair's two normals, and whether they are sure.
+template <int DT>
+__device__ __forceinline__ uint32_t normal_pair16(uint32_t xa, uint32_t xb, float p0, float p1, bool& sure) {
+    constexpr float kLow = 1.0f - 0x1.4p-21f, kHigh = 1.0f + 0x1.4p-21f;
+    bool sure_rho, sure_angle;
+    const float rho = rho32<DeviceSeed>(xa, sure_rho);
+    float sn, cs;
+    sincos32(xb, sn, cs, sure_angle);
+    const float zc = rho * cs, zs = rho * sn;
+    const uint32_t lo = pack16<DT>(fmaf(zc * kLow, p1, p0), fmaf(zs * kLow, p1, p0));
+    const uint32_t hi = pack16<DT>(fmaf(zc * kHigh, p1, p0), fmaf(zs * kHigh, p1, p0));
+    sure = sure_rho && sure_angle && lo == hi;
+    return lo;
+}
+
+// Block t of the output by the binary64 path.
+template <int DT>
+__device__ void normal_block64(void* dst, uint64_t n, float p0, float p1, uint32_t k0, uint32_t k1, uint32_t stream_id,
+                               uint32_t sub, uint64_t b_first, uint64_t t) {
+    const uint64_t b = b_first + t;
+    const u32x4 w = philox4x32_10({(uint32_t)b, (uint32_t)(b >> 32), sub, stream_id}, k0, k1);
+    float z[4], v[4];
+    box_muller(w.x, w.y, z[0], z[1]);
+    box_muller(w.z, w.w, z[2], z[3]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = fmaf(z[i], p1, p0);
+    if (t < n >> 2) {
+        store_four<DT>(dst, 4 * t, v, w);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (4 * t + i < n) store_one<DT>(dst, 4 * t + i, v[i], 0u);
+    }
+}
+
+// Launched from 2^20 blocks (4 million values) on: below that a thread of the
+// persistent grid (8 work-groups per CU) has one block at most, and the list's
+// pass over a few entries costs what the first pass saves (us, without -> with
+// the first pass: 2^21 fp16 values 6.6 -> 7.4, 2^22 10.7 -> 9.9, 2^23 19.1 ->
+// 14.8, 2^25 59.2 -> 38.7).
+constexpr uint64_t kNormal16Blocks = 1u << 20;
+constexpr uint64_t kNormal16Grid = 2048;
+constexpr uint32_t kRedo = 1024;  // blocks a work-group's list holds
+
+// The offset is a multiple of 4 (blocks and groups of four outputs coincide).
+template <int DT>
+__global__ __launch_bounds__(256) void gen_normal16_kernel(void* __restrict__ dst, uint64_t n, float p0, float p1,
+                                                           uint32_t k0, uint32_t k1, uint32_t stream_id, uint32_t sub,
+                                                           uint64_t b_first) {
+    __shared__ uint64_t s_redo[kRedo];
+    __shared__ uint32_t s_count;
+    if (threadIdx.x == 0) s_count = 0u;
+    __syncthreads();
+    const uint64_t n_blocks = (n + 3) >> 2, n_whole = n >> 2;
+    const uint64_t step = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n_blocks; t += step) {
+        const uint64_t b = b_first + t;
+        const u32x4 w = philox4x32_10({(uint32_t)b, (uint32_t)(b >> 32), sub, stream_id}, k0, k1);
+        bool sure0, sure1;
+        const uint32_t h0 = normal_pair16<DT>(w.x, w.y, p0, p1, sure0);
+        const uint32_t h1 = normal_pair16<DT>(w.z, w.w, p0, p1, sure1);
+        if (sure0 && sure1 && t < n_whole) {
+            ((uint2*)dst)[t] = make_uint2(h0, h1);
+        } else {
+            const uint32_t i = atomicAdd(&s_count, 1u);
+            if (i < kRedo) s_redo[i] = t;
+            else normal_block64<DT>(dst, n, p0, p1, k0, k1, stream_id, sub, b_first, t);  // (list full)
+        }
+    }
+    __syncthreads();
+    const uint32_t count = min(s_count, kRedo);
+    for (uint32_t i = threadIdx.x; i < count; i += blockDim.x)
+        normal_block64<DT>(dst, n, p0, p1, k0, k1, stream_id, sub, b_first, s_redo[i]);
+}
+
 template <int DIST, int DT>
 hipError_t launch_typed(void* dst, uint64_t n, float p0, float p1, uint64_t seed,
                         uint32_t stream_id, uint32_t sub, uint64_t offset, hipStream_t stream) {
@@ -119,6 +231,16 @@ hipError_t launch_typed(void* dst, uint64_t n, float p0, float p1, uint64_t seed
     const uint64_t b_last = (offset + n - 1) / 4;
     const uint64_t n_blocks = b_last - b_first + 1;
     const uint64_t want = (n_blocks + 255) / 256;
+    if constexpr (DIST == KB_DIST_NORMAL && DT != DT_F32) {
+        if ((offset & 3u) == 0 && n_blocks >= kNormal16Blocks) {
+            // up to 256 blocks a thread, so that the list (about one block in
+            // 150 of fp16, fewer of bf16) stays well under its length
+            const uint64_t grid16 = std::max<uint64_t>(kNormal16Grid, (want + 255) / 256);
+            hipLaunchKernelGGL((gen_normal16_kernel<DT>), dim3((unsigned)std::min(want, grid16)), dim3(256), 0, stream,
+                               dst, n, p0, p1, (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, sub, b_first);
+            return hipGetLastError();
+        }
+    }
     const unsigned grid = (unsigned)(want < 16384 ? want : 16384);
     hipLaunchKernelGGL((gen_kernel<DIST, DT>), dim3(grid), dim3(256), 0, stream, dst, n, p0, p1,
                        (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, sub, offset, b_first,

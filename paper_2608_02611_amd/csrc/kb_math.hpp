@@ -125,6 +125,52 @@ KB_MATH void box_muller64(uint32_t xa, uint32_t xb, double& zc, double& zs) {
     zs = rho * s;
 }
 
+// The same pair in binary32, for results that are stored in 16 bits.
+//
+// rho = sqrt(-2 ln u): u rounded to 24 bits as f, log2 of f 2^-32 by the
+// hardware (v_log_f32), and the rounding of u put back to first order where
+// it matters: log2(u) - log2(f 2^-32) = lo log2(e) / v, lo = v - f, with
+// 1 / u taken as 2 - u (exact to (1 - u)^2 where the logarithm goes to zero;
+// below u = 1/2 the term is under 2^-24 of the logarithm anyway).
+// Largest error over all 2^32 words, against the binary64 functions: rho
+// 2^-22.6 of its value wherever it is sure (1 - u above 2^-23), sin and cos
+// 2^-22.3.
+template <class Seed>
+KB_MATH float rho32(uint32_t x, bool& sure) {
+    const uint32_t v = x + 1u;  // (0 for u = 1: f = 0, not sure)
+    const float f = (float)v;
+    const float u = f * 0x1p-32f;
+    const float lo = (float)(int32_t)(v - Seed::to_u32(f));
+    const float L = __builtin_fmaf(lo * 0x1.715476p-32f, 2.0f - u, Seed::log2(u));  // log2(u) <= 0
+    sure = L < -0x1p-21f && v != 0u;
+    return Seed::sqrt32(L * -0x1.62e43p+0f);
+}
+
+// sin and cos of 2 pi x 2^-32 in binary32: the quadrant and the remainder r
+// (|r| <= pi / 4) come from the integer, so the relative error holds at the
+// zeros too.  sin r = r + r z (S0 + S1 z + S2 z^2) (minimax, 2^-28), cos r =
+// 1 - z / 2 + z^2 (C0 + C1 z + C2 z^2) (2^-33), z = r^2.  Not sure next to a
+// multiple of pi / 2, where the binary64 path's rounding of theta shows.
+KB_MATH void sincos32(uint32_t x, float& sn, float& cs, bool& sure) {
+    const uint32_t q = ((x >> 29) + 1u) >> 1;
+    const int32_t ri = (int32_t)(x - (q << 30));
+    sure = (uint32_t)(ri + 16) >= 32u;
+    const float r = (float)ri * 0x1.921fb6p-30f;
+    const float z = r * r;
+    float S = __builtin_fmaf(-0x1.994388p-13f, z, 0x1.11073ap-7f);
+    S = __builtin_fmaf(S, z, -0x1.555546p-3f);
+    const float s = __builtin_fmaf(r * z, S, r);
+    float C = __builtin_fmaf(0x1.99eb4ap-16f, z, -0x1.6c0c32p-10f);
+    C = __builtin_fmaf(C, z, 0x1.55554ap-5f);
+    C = __builtin_fmaf(C, z, -0.5f);
+    const float c = __builtin_fmaf(C, z, 1.0f);
+    const bool odd = (q & 1u) != 0u;
+    const uint32_t sb = __builtin_bit_cast(uint32_t, odd ? c : s);
+    const uint32_t cb = __builtin_bit_cast(uint32_t, odd ? s : c);
+    sn = __builtin_bit_cast(float, sb ^ ((q << 30) & 0x80000000u));
+    cs = __builtin_bit_cast(float, cb ^ (((q + 1u) << 30) & 0x80000000u));
+}
+
 // Student-t with 3 degrees of freedom of one block's words x, y, z (, w): the
 // ratio of the first normal to the root of the other three's mean square (a
 // chi-square over its degrees of freedom).  With T1, T2 = -2 ln u of the two

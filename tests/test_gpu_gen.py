@@ -50,6 +50,9 @@ CASES = [
 ]
 
 
+N16 = 1 << 22  # 16-bit normals: the first pass from this many values on
+
+
 @pytest.mark.parametrize("case", CASES)
 def test_u32_bit_exact(dev, case):
     n, seed, sid, sub, off = case
@@ -98,6 +101,23 @@ def test_normal_16bit_rounds_the_same_binary32_value(dev, dt):
     same = g32.view(np.uint32) == o32.view(np.uint32)
     assert np.array_equal(g16[same], o16[same])
     assert np.all(np.abs(g16[~same].astype(np.int32) - o16[~same].astype(np.int32)) <= 1)
+
+
+@pytest.mark.parametrize("dt", ["f16", "bf16"])
+@pytest.mark.parametrize("n,offset", [(N16, 0), (N16 - 4, 0), (N16 + 1, 8), (3 * N16 + 2, 4), (3 * N16 + 3, 0),
+                                      (N16 + 7, 3), (4 * N16, 1 << 34)])
+@pytest.mark.parametrize("p0,p1", [(0.0, 1.0), (0.0, 64.0), (3.0, -0.125), (0.0, 2.0 ** -17), (1.0, 0.0), (0.0, 3e38)])
+def test_normal_16bit_first_pass(dev, dt, n, offset, p0, p1):
+    """From N16 values on, a binary32 pass stores the 16-bit normals whose
+    bits it is sure of and leaves the others to the binary64 path: every bit
+    must be that of the binary32 stream (which takes the binary64 path only)
+    rounded to 16 bits, also in subnormals, at overflow and with no scale."""
+    print("normal first pass", dt, n, offset, p0, p1, flush=True)
+    f = torch.empty(n, dtype=torch.float32, device=dev)
+    kb.kb_gen_inputs(f, kb.KB_DIST_NORMAL, p0, p1, seed=77, stream_id=5, sub=2, offset=offset)
+    got = torch.empty(n, dtype={"f16": torch.float16, "bf16": torch.bfloat16}[dt], device=dev)
+    kb.kb_gen_inputs(got, kb.KB_DIST_NORMAL, p0, p1, seed=77, stream_id=5, sub=2, offset=offset)
+    assert torch.equal(got.view(torch.int16), f.to(got.dtype).view(torch.int16))
 
 
 @pytest.mark.parametrize("dist,dt,n", [("normal", "f32", 1 << 30), ("uniform", "f32", 1 << 30),
