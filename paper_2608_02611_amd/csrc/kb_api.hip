@@ -242,11 +242,16 @@ bool make_plan(int n_cands, int n_acc, uint64_t numel, int dtype, int resident_b
     //    over the chunks -- unless a tuning override sets the total; at most
     //    about 4096 work-groups in all;
     //  - fail-fast launch (serial_groups): the groups are screened in rounds
-    //    of ff_round groups, one round after another, and a round is one
-    //    set of resident work-groups (stripes = resident / ff_round, at most
-    //    2048).  Measured on the 16- and 64-candidate workloads, rounds of 2
-    //    groups balance best: with 1 the reference is re-read once per group,
-    //    with all groups in one round the work-groups of failed groups idle;
+    //    of ff_round groups, one round after another.  Up to 4 groups: rounds
+    //    of 2, a round one set of resident work-groups (16 x 2^24 bf16, most
+    //    failing: 68 us; in one round of 4: 103).  More: equal rounds of at
+    //    most 8 and stripes for two sets of resident work-groups, so that the
+    //    failures of 8 groups are found in one start and those that wait take
+    //    the places of the failed groups' (us, rounds of 2 -> this; with one
+    //    set of work-groups): 64 x 2^24 fp16 279 -> 255 (248), 64 x 2^22 bf16
+    //    151 -> 122 (106), 64 x 2^21 fp32 124 -> 87 (78), 32 x 2^22 fp32, none
+    //    failing, 117 -> 106 (101); but one passing of 64 x 2^24 fp16 103 ->
+    //    103 (117): a lone live group needs the work-groups;
     //  - the workspace is laid out for the bound C_ws, independent of the
     //    device, and the launch never exceeds it.
     const uint64_t n_chunks = numel / 512;
@@ -262,9 +267,16 @@ bool make_plan(int n_cands, int n_acc, uint64_t numel, int dtype, int resident_b
     const uint64_t c_ws = clamp_c(c_plain > 2048 ? c_plain : 2048);
     if (c_ws > (1u << 20)) return false;
     int blocks_total = tuning().blocks_total;
-    const int ff_round = tuning().ff_round > 0 ? tuning().ff_round : kFailFastRound;
-    if (blocks_total <= 0) blocks_total = resident_blocks > 0 ? resident_blocks : 2048;
     const int groups = P.n_groups > 0 ? P.n_groups : 1;
+    const bool long_round = groups > kFailFastShort;
+    const int n_rounds = (groups + kFailFastLong - 1) / kFailFastLong;
+    const int ff_round = tuning().ff_round > 0 ? tuning().ff_round
+                         : long_round          ? (groups + n_rounds - 1) / n_rounds
+                                               : kFailFastRound;
+    if (blocks_total <= 0) {
+        blocks_total = resident_blocks > 0 ? resident_blocks : 2048;
+        if (serial_groups && long_round) blocks_total *= 2;
+    }
     P.ff_round = ff_round < groups ? ff_round : groups;
     uint64_t C;
     if (serial_groups) {

@@ -575,8 +575,8 @@ __device__ __forceinline__ void clear_ff_words(const ScreenParams& p, int j0, in
 // The launch's parameters, read from the kernel argument segment (whose first
 // argument they are) where this is called: read at the start of the kernel and
 // kept, the finish's pointers and sizes take 40 scalar registers that the loop
-// over the chunks then keeps in vector lanes (two to seven spill moves per
-// candidate and chunk in the fp16 builds, none with the plain ones now).
+// over the chunks then keeps in vector lanes (13 or 14 spill moves per
+// candidate and chunk in the plain fp16 builds, 0 or 1 this way).
 __device__ __forceinline__ const ScreenParams& late_params() {
     auto args = __builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(args));

@@ -314,3 +314,33 @@ def test_rejected_and_empty(dev):
     a, _ = kb.screen(e, [e.clone()], ATOL, RTOL, 0)
     b, _ = kb.screen(e, [e.clone()], ATOL, RTOL, FF)
     assert same_bits(a[0], b[0])
+
+
+@pytest.mark.parametrize("K", [16, 17, 32, 36, 37, 65])
+def test_rounds_of_groups(dev, K):
+    """Four groups are screened in rounds of 2, more in equal rounds of up to 8
+    (5, 8, 9 -> 5 + 4, 10 -> 5 + 5 and 17 groups of 4), the last round with a
+    group of one candidate.  Failing candidates fill whole groups, parts of
+    groups, and the last."""
+    n = 300 * 1024 + 77
+    rng = np.random.default_rng(K)
+    r32 = rng.standard_normal(n).astype(np.float32) + np.float32(2.0)
+    cands = [(r32 * (1 + np.float32(1e-6) * rng.uniform(-1, 1, n).astype(np.float32))) for _ in range(K)]
+    for k in range(K):
+        if 4 <= k < 8 or k % 5 == 3 or k == K - 1:
+            cands[k] = cands[k].copy()
+            cands[k][rng.integers(0, n) if k % 2 else slice(None)] += np.float32(1.0)
+    say("fail-fast rounds", K, n)
+    ref = to_dev(r32, "f32", dev)
+    cd = [to_dev(c, "f32", dev) for c in cands]
+    full, fsum = kb.screen(ref, cd, ATOL, RTOL, 0)
+    orc = oracle_records(ref, cd, ATOL, RTOL, 0)
+    assert_records_match(full, orc, "rounds full")
+    for _ in range(2):
+        fast, ssum = kb.screen(ref, cd, ATOL, RTOL, FF)
+        assert ssum == fsum, (ssum, fsum)
+        for k, (g, f, o) in enumerate(zip(fast, full, orc)):
+            if o["mismatches"] == 0:
+                assert same_record(g, f), (k, g, f)
+            else:
+                check_partial(g, o, "rounds K=%d cand %d" % (K, k))
