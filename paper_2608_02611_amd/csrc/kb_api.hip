@@ -200,11 +200,14 @@ int plan_group_size(int n_cands, uint64_t numel, int dtype, bool fail_fast) {
     //   64 x 2^20 fp16 (128 MiB) 34.7 -> 35.7 -> 52.7;
     // fail-fast, whose rounds hold few groups: 64 x 65536 fp16 20.7 -> 11.9 ->
     //   11.1; 16 x 2^19 fp16 (16 MiB) 16.3 -> 15.1 -> 18.8; 16 x 2^20 fp16
-    //   (32 MiB) 20.1 -> 25.5 -> 29.1.
+    //   (32 MiB) 20.1 -> 25.5 -> 29.1;
     const uint64_t limit1 = fail_fast ? 8u << 20 : 16u << 20, limit2 = fail_fast ? 16u << 20 : 64u << 20;
     const uint64_t one = (uint64_t)n_cands * elem_size(dtype);  // bytes of one element of every candidate
-    if (numel <= limit1 / one) kg_cap = 1;
-    else if (numel <= limit2 / one) kg_cap = 2;
+    // and at most 128 groups, since each takes at least 8 work-groups and
+    // the device holds 1024.
+    constexpr int kSmallGroups = 128;
+    if (n_cands <= kSmallGroups && numel <= limit1 / one) kg_cap = 1;
+    else if (n_cands <= 2 * kSmallGroups && numel <= limit2 / one) kg_cap = 2;
     if (tuning().kg_cap > 0) kg_cap = tuning().kg_cap;
     int kg = 1;
     while (kg < n_cands && kg < kg_cap) kg *= 2;

@@ -270,6 +270,16 @@ def test_large_calls_need_a_host_table(L):
     assert "workspace of 16 bytes" in kb.kb_last_error()
 
 
+@pytest.mark.parametrize("n", [1, 4096, 16384, 65536])
+def test_small_groups_only_for_short_lists(L, n):
+    """A group takes at least 8 work-groups: lists of more than 128 (256)
+    candidates are not split into groups of 1 (2), however small."""
+    for K in (1, 128, 129, 256, 257, 1024, 1 << 22):
+        plan = kb.kb_screen_launch(K, n, kb.KB_F32)
+        assert plan["group_size"] >= (1 if K <= 128 else 2 if K <= 256 else 4), (K, n, plan)
+        assert plan["grid"] * plan["threads"] < 1 << 32, (K, n, plan)
+
+
 def test_positions_argument_errors(L):
     """kb_screen_ex with positions (opts.d_loc): its own workspace size, and
     the refusals that come before any device work."""
