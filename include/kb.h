@@ -225,7 +225,8 @@ int kb_policy_check(const kb_tensor* ref, const kb_tensor* cands, int n_cands,
 
 /* Bytes of device workspace kb_screen needs for n_cands candidates of numel
  * elements of dtype (0 on invalid arguments).  A pure function of its
- * arguments (no device query). */
+ * arguments (no device query) that never falls as numel grows: a workspace
+ * for the largest tensor serves smaller ones (zero-filled between sizes). */
 size_t kb_screen_workspace_bytes(int n_cands, uint64_t numel, int dtype);
 
 /* Bytes of device workspace a kb_screen_ex call with positions (opts->d_loc)

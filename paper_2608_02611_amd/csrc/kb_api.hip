@@ -2,7 +2,6 @@
 // validation, the policy gate, launch planning and the statistics readback.
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
 #include <atomic>
 #include <chrono>
 #include <cmath>
@@ -181,12 +180,21 @@ int resident_blocks(int dtype, int kg, bool fail_fast = false, bool wide = false
         return 0;
     return cus * screen_blocks_per_cu(dtype, kg, fail_fast, wide, loc);
 }
+// Groups of at most `cap` candidates (a power of two).
+int group_size(int n_cands, int cap) {
+    if (tuning().kg_cap > 0) cap = tuning().kg_cap;
+    int kg = 1;
+    while (kg < n_cands && kg < cap) kg *= 2;
+    return kg;
+}
+
+// Candidates per group of long passes, measured on the five screening
+// workloads: groups of 4 for fp32 and for short candidate lists, 8 for long
+// lists of 16-bit tensors (the reference is then re-read by fewer groups).
+int long_group_size(int n_cands, int dtype) { return group_size(n_cands, dtype != DT_F32 && n_cands >= 32 ? 8 : 4); }
+
 int plan_group_size(int n_cands, uint64_t numel, int dtype, bool fail_fast) {
     if (n_cands < 1) return 1;  // (no plan; the caller reports it)
-    // Long passes, measured on the five screening workloads: groups of 4 for
-    // fp32 and for short candidate lists, 8 for long lists of 16-bit tensors
-    // (the reference is then re-read by fewer groups).
-    int kg_cap = (dtype != DT_F32 && n_cands >= 32) ? 8 : 4;
     // Short passes are bound by latency, not bandwidth: each wave visits a
     // few chunks at most, so the time is that of the kernel's code run about
     // once -- the chain through all candidates of the group and the fetch of
@@ -207,12 +215,9 @@ int plan_group_size(int n_cands, uint64_t numel, int dtype, bool fail_fast) {
     // the device holds 1024 (1024 x 4096 fp32 32 us in groups of 4, 60 in
     // groups of 1; 200 x 4096 16.7 in groups of 2, 19.0 in groups of 1).
     constexpr int kSmallGroups = 128;
-    if (n_cands <= kSmallGroups && numel <= limit1 / one) kg_cap = 1;
-    else if (n_cands <= 2 * kSmallGroups && numel <= limit2 / one) kg_cap = 2;
-    if (tuning().kg_cap > 0) kg_cap = tuning().kg_cap;
-    int kg = 1;
-    while (kg < n_cands && kg < kg_cap) kg *= 2;
-    return kg;
+    if (n_cands <= kSmallGroups && numel <= limit1 / one) return group_size(n_cands, 1);
+    if (n_cands <= 2 * kSmallGroups && numel <= limit2 / one) return group_size(n_cands, 2);
+    return long_group_size(n_cands, dtype);
 }
 
 bool make_plan(int n_cands, int n_acc, uint64_t numel, int dtype, int resident_blocks,
@@ -226,15 +231,13 @@ bool make_plan(int n_cands, int n_acc, uint64_t numel, int dtype, int resident_b
     P.numel = numel;
     const uint64_t vec = 16 / elem_size(dtype);
     P.n_vec = numel / vec;
-    // Candidates per group (chosen from n_cands so that the workspace sized
-    // for n_cands always suffices).  The plain and the fail-fast launch may
-    // group differently; the workspace is laid out for both.
+    // Candidates per group.  The workspace is laid out for the largest groups
+    // of these n_cands candidates (those of long passes), in a layout that
+    // serves smaller ones too, so its size grows with numel whatever groups
+    // a call takes.
     P.kg = plan_group_size(n_cands, numel, dtype, serial_groups);
-    const int kg_plain = plan_group_size(n_cands, numel, dtype, false);
-    const int kg_ff = plan_group_size(n_cands, numel, dtype, true);
-    const int groups_plain = (n_cands + kg_plain - 1) / kg_plain, groups_ff = (n_cands + kg_ff - 1) / kg_ff;
-    const int groups_max = std::max(groups_plain, groups_ff);
-    const int slots_max = std::max(groups_plain * kg_plain, groups_ff * kg_ff);
+    const int kg_ws = long_group_size(n_cands, dtype);
+    const int groups_ws = (n_cands + kg_ws - 1) / kg_ws;
     P.n_groups = n_acc > 0 ? (n_acc + P.kg - 1) / P.kg : 0;
     // Work-groups per candidate group (stripes; a multiple of 8, the XCD count):
     //  - at least enough that one work-group sees fewer than 2^31 elements
@@ -267,8 +270,9 @@ bool make_plan(int n_cands, int n_acc, uint64_t numel, int dtype, int resident_b
         if (c < 8) c = 8;
         return c;
     };
-    const uint64_t c_plain = clamp_c(align_up((4096 + groups_plain - 1) / groups_plain, 8));
-    const uint64_t c_ws = clamp_c(c_plain > 2048 ? c_plain : 2048);
+    const int groups_call = (n_cands + P.kg - 1) / P.kg;
+    const uint64_t c_plain = clamp_c(align_up((4096 + groups_call - 1) / groups_call, 8));
+    const uint64_t c_ws = clamp_c(groups_ws == 1 ? 4096 : 2048);
     if (c_ws > (1u << 20)) return false;
     int blocks_total = tuning().blocks_total;
     const int groups = P.n_groups > 0 ? P.n_groups : 1;
@@ -294,31 +298,24 @@ bool make_plan(int n_cands, int n_acc, uint64_t numel, int dtype, int resident_b
     if (C < 8) C = 8;
     P.blocks_per_group = (int)C;
     const uint64_t Cw = c_ws;  // layout stride bound
-    // Workspace layout, sized for the group count of n_cands.  The tagged
-    // tickets (8 bytes each) come first, then the fail-fast words (one
-    // 128-byte line each).
+    // Workspace layout, per candidate, so that it holds any grouping: the
+    // tagged tickets (8 bytes each) come first, then the fail-fast words (one
+    // 128-byte line each) -- what must begin at zero --, then the partials.
     P.n_super = (int)((C + 15) / 16);
     const int super_ws = (int)((Cw + 15) / 16);
     size_t off = 0;
-    P.off_tickets2 = off;
-    off += (size_t)groups_max * 8;
-    P.off_tickets1 = off;
-    off += (size_t)groups_max * super_ws * 8;
-    off = align_up(off, 256);
+    P.off_tickets = off;
+    off = align_up(off + (size_t)n_cands * (size_t)(super_ws + (super_ws > 1)) * 8, 256);
     P.off_ff_flags = off;
-    off = align_up(off + (size_t)slots_max * (size_t)(1 + super_ws) * 128, 256);
+    off = align_up(off + (size_t)groups_ws * kg_ws * (size_t)(1 + super_ws) * 128, 256);
     P.off_part_u32 = off;
     off = align_up(off + (size_t)kPartPlanes * n_cands * Cw * 4, 256);
     P.off_part_ssd = off;
     off = align_up(off + (size_t)n_cands * Cw * 8, 256);
     P.off_part_ssr = off;
-    off = align_up(off + (size_t)groups_max * Cw * 8, 256);
-    P.off_part_ssrc = off;
     off = align_up(off + (size_t)n_cands * Cw * 8, 256);
     P.off_part2 = off;
     off = align_up(off + (size_t)n_cands * super_ws * sizeof(Part2), 256);
-    P.off_part2_ssr = off;
-    off = align_up(off + (size_t)groups_max * super_ws * 8, 256);
     P.core_total = off;
     P.off_part_idx = off;
     off = align_up(off + (size_t)IX_COUNT * n_cands * Cw * 8, 256);
@@ -430,15 +427,12 @@ int screen_with_status(const char* who, const kb_tensor* ref, const kb_tensor* c
     p.n_super = P.n_super;
     p.ff_round = P.ff_round;
     p.tag = call_tag();
-    p.tickets1 = (uint64_t*)(ws + P.off_tickets1);
-    p.tickets2 = (uint64_t*)(ws + P.off_tickets2);
+    p.tickets = (uint64_t*)(ws + P.off_tickets);
     p.ff_flags = (uint32_t*)(ws + P.off_ff_flags);
     p.part_u32 = (uint32_t*)(ws + P.off_part_u32);
     p.part_ssd = (double*)(ws + P.off_part_ssd);
     p.part_ssr = (double*)(ws + P.off_part_ssr);
-    p.part_ssrc = (double*)(ws + P.off_part_ssrc);
     p.part2 = (Part2*)(ws + P.off_part2);
-    p.part2_ssr = (double*)(ws + P.off_part2_ssr);
     p.part_idx = loc ? (uint64_t*)(ws + P.off_part_idx) : nullptr;
     p.part2_idx = loc ? (Part2Idx*)(ws + P.off_part2_idx) : nullptr;
     p.stats = d_stats;

@@ -52,8 +52,8 @@ struct ScreenPlan {
     int wide;             // launch the 5-waves-per-SIMD build (use_wide_kernel)
     // workspace byte offsets; core_total ends what every call uses, total
     // adds the position-search partials (calls with positions only)
-    size_t off_tickets1, off_tickets2, off_ff_flags, off_table, off_part_u32, off_part_ssd,
-        off_part_ssr, off_part_ssrc, off_part2, off_part2_ssr, core_total, off_part_idx, off_part2_idx, total;
+    size_t off_tickets, off_ff_flags, off_part_u32, off_part_ssd, off_part_ssr, off_part2, core_total, off_part_idx,
+        off_part2_idx, total;
 };
 
 // Position-search partials: per (work-group, candidate), the smallest
@@ -70,7 +70,7 @@ struct Part2 {
     uint32_t maxabs, maxrel, bitdiff, pad;
     double ssd;
     uint64_t nread;  // fail-fast only: elements compared
-    double ssr;      // fail-fast only: the candidate's own sum of r^2
+    double ssr;      // sum of r^2 (the group's; fail-fast: over what the candidate was compared with)
 };
 
 // Launch geometry and workspace layout.  The layout depends only on
@@ -133,15 +133,13 @@ struct ScreenParams {
     int n_super;
     int ff_round;        // fail-fast: candidate groups per round of the grid
     uint32_t tag;        // this call's tag (nonzero): marks its tickets and fail-fast words
-    uint64_t* tickets1;  // [n_groups][n_super] tagged tickets: (tag << 32) | arrivals
-    uint64_t* tickets2;  // [n_groups]
+    uint64_t* tickets;   // tagged tickets, (tag << 32) | arrivals: [n_groups][n_super], then (n_super > 1) [n_groups]
     uint32_t* ff_flags;  // fail-fast words: [n_groups * KG][1 + n_super] lines of 32 words
     uint32_t* part_u32;  // [kPartPlanes][n_acc][blocks_per_group]
     double* part_ssd;    // [n_acc][blocks_per_group]
-    double* part_ssr;    // [n_groups][blocks_per_group]
-    double* part_ssrc;   // fail-fast: [n_acc][blocks_per_group] per-candidate sums of r^2
+    double* part_ssr;    // sums of r^2: [n_groups][blocks_per_group]; fail-fast, per candidate:
+                         // [n_acc][blocks_per_group]
     Part2* part2;        // [n_acc][n_super]
-    double* part2_ssr;   // [n_groups][n_super]
     uint64_t* part_idx;  // positions: [IX_COUNT][n_acc][blocks_per_group]
     Part2Idx* part2_idx; // positions: [n_acc][n_super]
     kb_stats* stats;     // caller's records, indexed by CandEntry::index

@@ -567,6 +567,17 @@ __device__ __forceinline__ uint32_t* ff_word(const ScreenParams& p, int slot, in
     return p.ff_flags + ((size_t)slot * (size_t)(1 + p.n_super) + (size_t)line) * 32u;
 }
 
+// The tagged tickets of candidate group g: super-group m's, and the group's.
+// (In the second halves of the fail-fast lines they would need no memory of
+// their own, but atomics on polled lines cost a fail-fast screen of 64 x 2^22
+// fp32, none failing, 202 us instead of 184.)
+__device__ __forceinline__ uint64_t* super_ticket(const ScreenParams& p, int g, int m) {
+    return p.tickets + (size_t)g * (size_t)p.n_super + m;
+}
+__device__ __forceinline__ uint64_t* group_ticket(const ScreenParams& p, int g) {
+    return p.tickets + (size_t)p.n_groups * (size_t)p.n_super + g;
+}
+
 // Zero the fail-fast words of a candidate group (its finisher, once every
 // work-group of the group is past its last poll).
 __device__ __forceinline__ void clear_ff_words(const ScreenParams& p, int j0, int kgs) {
@@ -626,11 +637,9 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
     __shared__ NonFinite s_nf[kWaves][KG];
     __shared__ uint32_t s_rel[KG];  // work-group max-rel values (binary32 bits)
     __shared__ uint32_t s_arrival;  // this work-group's ticket (0: the workspace was not clean)
-    __shared__ double s_sr1;        // single-level finish: the group's sum of r^2
     // fail-fast: per wave and candidate, elements compared and their sum of r^2
     __shared__ uint32_t s_nread[FF ? kWaves : 1][FF ? KG : 1];
     __shared__ double s_ssrc[FF ? kWaves : 1][FF ? KG : 1];
-    __shared__ double s_sr1c[FF ? KG : 1];  // single-level finish, per candidate
     __shared__ uint32_t s_told[FF ? KG : 1];  // fail-fast: the work-group knows candidate j failed
     __shared__ uint64_t s_idx[LOC ? kWaves : 1][LOC ? KG : 1][IX_COUNT];  // positions per wave
     __shared__ Found s_found[LOC ? KG : 1];  // the finisher's combined positions
@@ -1095,7 +1104,7 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
                 src += s_ssrc[w][j];
             }
             st_coherent(&p.part_u32[PF_NREAD * plane + row], nr);
-            st_coherent(&p.part_ssrc[row], src);
+            st_coherent(&p.part_ssr[row], src);
         }
         if constexpr (LOC) {
             // the smallest index among the waves that hold each maximum
@@ -1119,7 +1128,7 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
         st_coherent(&p.part_u32[PF_BITDIFF * plane + row], bd);
         st_coherent(&p.part_ssd[row], sd);
     }
-    if (threadIdx.x == 0) {
+    if (!FF && threadIdx.x == 0) {
         double sr = 0.0;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) sr += s_ssr[w];
@@ -1138,7 +1147,7 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
     const int msize = min(16, C - 16 * m);
     complete_stores();
     __syncthreads();
-    if (threadIdx.x == 0) s_arrival = ticket_arrive(&p.tickets1[(size_t)g * S + m], p.tag);
+    if (threadIdx.x == 0) s_arrival = ticket_arrive(super_ticket(p, g, m), p.tag);
     __syncthreads();
     if (s_arrival != (uint32_t)msize) {
         if (s_arrival == 0u) report_dirty(p, table_of(p, tab), g, j0, kg);
@@ -1153,10 +1162,12 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
         const int s = 16 * m + sl;
         uint64_t mi = 0, na = 0, pi = 0, ni = 0, nr = 0;
         uint32_t ma = 0, mr = 0, bd = 0;
-        double sd = 0.0, src = 0.0;
+        double sd = 0.0, sr = 0.0;
         uint64_t i0 = kNone, i1 = kNone, i2 = kNone;  // positions
         if (jj < kg) {
             const size_t idx = (size_t)(j0 + jj) * C + s;
+            // (every row of 16 lanes sums the group's r^2 itself)
+            if (have) sr = ld_coherent(&p.part_ssr[FF ? idx : (size_t)g * C + s]);
             if (LOC && have) {
                 i0 = ld_coherent(&p.part_idx[IX_FIRST_MISMATCH * plane + idx]);
                 i1 = ld_coherent(&p.part_idx[IX_MAX_ABS * plane + idx]);
@@ -1164,7 +1175,6 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
             }
             if (FF && have) {
                 nr = ld_coherent(&p.part_u32[PF_NREAD * plane + idx]);
-                src = ld_coherent(&p.part_ssrc[idx]);
             }
             if (have) {
                 mi = ld_coherent(&p.part_u32[PF_MISM * plane + idx]);
@@ -1185,6 +1195,7 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
             mr = row_max_u32(mr);
             bd = row_or_u32(bd);
             sd = row_sum_f64(sd);
+            sr = row_sum_f64(sr);
             if constexpr (LOC) {
                 i0 = row_min_u64(i0);
                 i1 = row_min_u64(ma_own == ma ? i1 : kNone);
@@ -1198,13 +1209,7 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
             }
             if constexpr (FF) {
                 nr = row_sum_u64(nr);
-                src = row_sum_f64(src);
-                if (sl == 0 && S > 1) {
-                    Part2* q = &p.part2[(size_t)(j0 + jj) * S + m];
-                    st_coherent(&q->nread, nr);
-                    st_coherent(&q->ssr, src);
-                }
-                if (sl == 0 && S == 1) s_sr1c[jj] = src;
+                if (sl == 0 && S > 1) st_coherent(&p.part2[(size_t)(j0 + jj) * S + m].nread, nr);
             }
             if (sl == 0 && S > 1) {
                 Part2* q = &p.part2[(size_t)(j0 + jj) * S + m];
@@ -1216,41 +1221,28 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
                 st_coherent(&q->maxrel, mr);
                 st_coherent(&q->bitdiff, bd);
                 st_coherent(&q->ssd, sd);
-            }
-        }
-        if (jj == 0) {
-            double sr = have ? ld_coherent(&p.part_ssr[(size_t)g * C + s]) : 0.0;
-            sr = row_sum_f64(sr);
-            if (sl == 0) {
-                if (S > 1) st_coherent(&p.part2_ssr[(size_t)g * S + m], sr);
-                else s_sr1 = sr;
+                st_coherent(&q->ssr, sr);
             }
         }
         if (S == 1) {
             // Single-level finish: the group has at most 16 stripes, and this
             // work-group has combined all of them.
-            __syncthreads();
             if (jj < kg && sl == 0) {
-                if constexpr (FF)
-                    write_record(&p.stats[table[j0 + jj].index], nr, mi, na, pi, ni, ma, mr, bd, sd,
-                                 s_sr1c[jj]);
-                else
-                    write_record(&p.stats[table[j0 + jj].index], p.numel, mi, na, pi, ni, ma, mr, bd,
-                                 sd, s_sr1);
+                write_record(&p.stats[table[j0 + jj].index], FF ? nr : p.numel, mi, na, pi, ni, ma, mr, bd, sd, sr);
                 if constexpr (LOC) s_found[jj] = Found{i0, i1, i2, ma};
             }
             if constexpr (LOC) write_positions<DT>(p, table, j0, kg, tfirst, s_found);
             if (g == 0) write_rejected(p, table);
-            if (threadIdx.x == 0) st_coherent(&p.tickets1[(size_t)g * S + m], (uint64_t)0);
+            if (threadIdx.x == 0) st_coherent(super_ticket(p, g, m), (uint64_t)0);
             if constexpr (FF) clear_ff_words(p, j0, KG);
             return;
         }
     }
-    if (threadIdx.x == 0) st_coherent(&p.tickets1[(size_t)g * S + m], (uint64_t)0);
+    if (threadIdx.x == 0) st_coherent(super_ticket(p, g, m), (uint64_t)0);
 
     complete_stores();
     __syncthreads();
-    if (threadIdx.x == 0) s_arrival = ticket_arrive(&p.tickets2[g], p.tag);
+    if (threadIdx.x == 0) s_arrival = ticket_arrive(group_ticket(p, g), p.tag);
     __syncthreads();
     if (s_arrival != (uint32_t)S) {
         if (s_arrival == 0u) report_dirty(p, table, g, j0, kg);
@@ -1260,24 +1252,22 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
     if (jj < kg) {
         uint64_t mi = 0, na = 0, pi = 0, ni = 0, nr = 0;
         uint32_t ma = 0, mr = 0, bd = 0;
-        double sd = 0.0, sr = 0.0, src = 0.0;
+        double sd = 0.0, sr = 0.0;
         uint64_t i0 = kNone, i1 = kNone, i2 = kNone;  // positions
         const Part2* row = p.part2 + (size_t)(j0 + jj) * S;
-        const double* rs = p.part2_ssr + (size_t)g * S;
         // U super-groups per lane in flight (fewer with positions, whose
         // partials are larger: this loop sets the kernel's register peak);
         // either way each lane adds its super-groups in increasing order
         constexpr int U = LOC ? 2 : 4;
         for (int q0 = sl; q0 < S; q0 += 16 * U) {
             Part2 v[U];
-            double w[U];
             Part2Idx vi[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int q = q0 + 16 * u;
                 if (FF && q < S) {
                     nr += ld_coherent(&row[q].nread);
-                    src += ld_coherent(&row[q].ssr);
+                    sr += ld_coherent(&row[q].ssr);
                 }
                 if (q < S) {
                     const Part2* e = &row[q];
@@ -1289,10 +1279,9 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
                     v[u].maxrel = ld_coherent(&e->maxrel);
                     v[u].bitdiff = ld_coherent(&e->bitdiff);
                     v[u].ssd = ld_coherent(&e->ssd);
-                    w[u] = ld_coherent(&rs[q]);
+                    if constexpr (!FF) v[u].ssr = ld_coherent(&e->ssr);
                 } else {
                     v[u] = Part2{0, 0, 0, 0, 0u, 0u, 0u, 0u, 0.0, 0, 0.0};
-                    w[u] = 0.0;
                 }
                 if constexpr (LOC) {
                     const Part2Idx* e = &p.part2_idx[(size_t)(j0 + jj) * S + q];
@@ -1318,7 +1307,7 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
                 mr = max(mr, v[u].maxrel);
                 bd |= v[u].bitdiff;
                 sd += v[u].ssd;
-                sr += w[u];
+                if constexpr (!FF) sr += v[u].ssr;
             }
         }
         mi = row_sum_u64(mi);
@@ -1337,16 +1326,9 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
             i2 = row_min_u64(mr_own == mr ? i2 : kNone);
             if (sl == 0) s_found[jj] = Found{i0, i1, i2, ma};
         }
-        if constexpr (FF) {
-            nr = row_sum_u64(nr);
-            src = row_sum_f64(src);
-            if (sl == 0)
-                write_record(&p.stats[table[j0 + jj].index], nr, mi, na, pi, ni, ma, mr, bd, sd, src);
-        } else {
-            if (sl == 0)
-                write_record(&p.stats[table[j0 + jj].index], p.numel, mi, na, pi, ni, ma, mr, bd, sd,
-                             sr);
-        }
+        if constexpr (FF) nr = row_sum_u64(nr);
+        if (sl == 0)
+            write_record(&p.stats[table[j0 + jj].index], FF ? nr : p.numel, mi, na, pi, ni, ma, mr, bd, sd, sr);
     }
     if constexpr (LOC) write_positions<DT>(p, table, j0, kg, tfirst, s_found);
     // Group 0's finisher also writes the rejected candidates' records.
@@ -1354,7 +1336,7 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
     // Leave the ticket and the failed words at zero (every work-group of the
     // group has finished reading them): the next call on this workspace then
     // finds them clean even if its tag happens to equal this call's.
-    if (threadIdx.x == 0) st_coherent(&p.tickets2[g], (uint64_t)0);
+    if (threadIdx.x == 0) st_coherent(group_ticket(p, g), (uint64_t)0);
     if constexpr (FF) clear_ff_words(p, j0, KG);
     }
 }

@@ -270,6 +270,33 @@ def test_large_calls_need_a_host_table(L):
     assert "workspace of 16 bytes" in kb.kb_last_error()
 
 
+@pytest.mark.parametrize("dt", [kb.KB_F32, kb.KB_F16, kb.KB_BF16])
+def test_workspace_grows_with_numel(L, dt):
+    """A workspace sized for the largest tensor serves every smaller one,
+    whatever groups the plan makes of the candidates at each size; and no
+    size exceeds that of the grouping of long passes (tickets and sums per
+    group of 4, or 8 for 32 or more 16-bit candidates)."""
+    es = 4 if dt == kb.KB_F32 else 2
+    for size in (kb.kb_screen_workspace_bytes, kb.kb_screen_positions_workspace_bytes):
+        for K in (1, 2, 3, 4, 5, 7, 8, 16, 31, 32, 33, 64, 100, 128, 129, 200, 256, 257, 1024):
+            ns = {(m << 20) // (K * es) + d for m in (1, 4, 8, 16, 32, 64, 128) for d in (0, 1, 512, 513)}
+            ns |= {(1 << e) + d for e in range(9, 34) for d in (0, 1)}
+            sizes = [size(K, n, dt) for n in sorted(ns)]
+            assert min(sizes) > 0 and sizes == sorted(sizes), (K, [n for n, b in zip(sorted(ns), sizes)])
+            kg = 1
+            while kg < min(K, 8 if K >= 32 and es == 2 else 4):
+                kg *= 2
+            groups = -(-K // kg)
+            for n, b in zip(sorted(ns), sizes):
+                cw = min(4096 if groups == 1 else 2048, -(-(-(-(n // 512) // 8)) // 8) * 8)
+                cw = max(cw, -(-(n // 2 ** 31 + 1) // 8) * 8, 8)
+                sup = -(-cw // 16)
+                most = groups * (8 + 8 * sup + kg * (1 + sup) * 128 + cw * 8 + sup * 8) + K * (cw * 48 + sup * 72)
+                if size is kb.kb_screen_positions_workspace_bytes:
+                    most += K * (cw + sup) * 24
+                assert b <= most + 12 * 256, (K, n, b, most)
+
+
 @pytest.mark.parametrize("n", [1, 4096, 16384, 65536])
 def test_small_groups_only_for_short_lists(L, n):
     """A group takes at least 8 work-groups: lists of more than 128 (256)

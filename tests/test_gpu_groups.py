@@ -79,3 +79,34 @@ def test_group_size_limits(dev, dt, K, limit, group, past):
         recs, _ = kb.kb_screen_stats(st, K)
         assert_records_match(recs, orc, "positions")
         assert kb.read_locate(d_loc, K) == locs
+
+
+@pytest.mark.parametrize("dt,K", [("f32", 3), ("f32", 9), ("bf16", 37)])
+def test_one_workspace_for_all_sizes(dev, dt, K):
+    """One workspace, sized for the largest tensor and zero-filled between
+    sizes, through every group size of the plan (groups of 1, 2 and 4 or 8
+    lay their tickets and sums in the same regions)."""
+    es = 4 if dt == "f32" else 2
+    atol, rtol = (1e-5, 1e-3) if dt == "f32" else (1e-3, 1e-2)
+    sizes = [m * MIB // (K * es) for m in (65, 64, 17, 15, 9, 7, 1)]
+    ws = torch.empty(kb.kb_screen_positions_workspace_bytes(K, sizes[0], CODE[dt]), dtype=torch.uint8, device=dev)
+    r, cs = tensors(dt, K, sizes[0])
+    seen = set()
+    for n in sizes:
+        print("one workspace", dt, K, n, flush=True)
+        seen.add(kb.kb_screen_launch(K, n, CODE[dt])["group_size"])
+        rn, cn = r[:n], [c[:n] for c in cs]
+        orc = oracle_records(rn, cn, atol, rtol, dt=dt)
+        locs = oracle_positions_host(rn, cn, dt, atol, rtol, orc)
+        ref, cands = to_device(rn, dt, dev), [to_device(c, dt, dev) for c in cn]
+        kb.kb_screen_workspace_init(ws)
+        st, _ = kb.kb_screen(ref, cands, atol, rtol, kb.KB_FAIL_FAST, ws)
+        recs, _ = kb.kb_screen_stats(st, K)
+        assert [g["passed"] for g in recs] == [o["passed"] for o in orc]
+        st, _ = kb.kb_screen(ref, cands, atol, rtol, 0, ws)
+        assert_records_match(kb.kb_screen_stats(st, K)[0], orc, "plain")
+        d_loc = kb.alloc_locate(K, dev)
+        st, _ = kb.kb_screen(ref, cands, atol, rtol, 0, ws, d_loc=d_loc)
+        assert_records_match(kb.kb_screen_stats(st, K)[0], orc, "positions")
+        assert kb.read_locate(d_loc, K) == locs
+    assert len(seen) >= 3, seen
