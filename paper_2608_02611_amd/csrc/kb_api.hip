@@ -220,6 +220,42 @@ int plan_group_size(int n_cands, uint64_t numel, int dtype, bool fail_fast) {
     return long_group_size(n_cands, dtype);
 }
 
+// Fail-fast launch: the groups are screened in rounds of `groups`, one round
+// after another; the stripes of a round are `sets` times the resident
+// work-groups (rounded down: one stripe too many starts another set).
+//
+// A group that has failed leaves its work-groups' places to those that wait.
+// Long rounds find the failures of many groups in one start; short ones give
+// a lone live group more of the device, and each round reads the reference
+// again.  So tensors up to 16 MiB, where a start counts most, take long
+// rounds; from 32 MiB on, where a lone group's share counts, shorter ones.
+// Measured over lists of 5 to 33 groups in which whole groups fail, half of
+// the candidates, all but one, or none; us, rounds of 2 first, for the kind
+// that gains least and the one that gains most:
+//   31 x 2^22 bf16 (8 groups, 8 MiB)  63 -> 52, 50 -> 33 in one round of 8;
+//   48 x 2^22 fp32 (12, 16 MiB)       159 -> 145, 78 -> 39 in rounds of 6;
+//   64 x 2^24 fp16 (8, 32 MiB)        265 -> 277, 212 -> 173 in one round of 8,
+//                  two sets (one set  265 -> 268 and 90 -> 106);
+//   31 x 2^25 fp32 (8, 128 MiB)       408 -> 380, 83 -> 76 in rounds of 4, two
+//                  sets (one round of 8, two sets: 83 -> 107);
+//   33 x 2^25 bf16 (5, 64 MiB), none failing 407 before; rounds of 4 and two
+//                  sets 397, one round of 5 430.
+// 16-bit lists in groups of 4 (up to 31 candidates) are bound by instructions
+// rather than memory, and no longer round is better for every kind (31 x 2^24
+// bf16: 122 -> 161, 59 -> 64 in one round of 8); nor is any for up to 4 groups
+// (16 x 2^24 bf16 64 -> 89, 9 x 2^22 30 -> 34): rounds of 2 there.
+struct FailFastRound {
+    int groups, sets;
+};
+FailFastRound fail_fast_round(int groups, int kg, uint64_t numel, int dtype) {
+    const uint64_t bytes = numel * elem_size(dtype);
+    const bool brief = bytes <= 16u << 20;
+    if (groups <= 4 || (!brief && dtype != DT_F32 && kg <= 4)) return {2, 1};
+    if (bytes > 32u << 20) return {4, 2};
+    const int rounds = (groups + 7) / 8;  // (equal ones)
+    return {(groups + rounds - 1) / rounds, brief ? 1 : 2};
+}
+
 bool make_plan(int n_cands, int n_acc, uint64_t numel, int dtype, int resident_blocks,
                bool serial_groups, ScreenPlan* plan) {
     if (n_cands < 1 || n_acc < 0 || n_acc > n_cands || !is_float_dtype(dtype)) return false;
@@ -248,17 +284,7 @@ bool make_plan(int n_cands, int n_acc, uint64_t numel, int dtype, int resident_b
     //    the candidate groups -- the grid is persistent, each wave strides
     //    over the chunks -- unless a tuning override sets the total; at most
     //    about 4096 work-groups in all;
-    //  - fail-fast launch (serial_groups): the groups are screened in rounds
-    //    of ff_round groups, one round after another.  Up to 4 groups: rounds
-    //    of 2, a round one set of resident work-groups (16 x 2^24 bf16, most
-    //    failing: 68 us; in one round of 4: 103).  More: equal rounds of at
-    //    most 8 and stripes for two sets of resident work-groups, so that the
-    //    failures of 8 groups are found in one start and those that wait take
-    //    the places of the failed groups' (us, rounds of 2 -> this; with one
-    //    set of work-groups): 64 x 2^24 fp16 279 -> 255 (248), 64 x 2^22 bf16
-    //    151 -> 122 (106), 64 x 2^21 fp32 124 -> 87 (78), 32 x 2^22 fp32, none
-    //    failing, 117 -> 106 (101); but one passing of 64 x 2^24 fp16 103 ->
-    //    103 (117): a lone live group needs the work-groups;
+    //  - fail-fast launch (serial_groups): see fail_fast_round;
     //  - the workspace is laid out for the bound C_ws, independent of the
     //    device, and the launch never exceeds it.
     const uint64_t n_chunks = numel / 512;
@@ -276,19 +302,16 @@ bool make_plan(int n_cands, int n_acc, uint64_t numel, int dtype, int resident_b
     if (c_ws > (1u << 20)) return false;
     int blocks_total = tuning().blocks_total;
     const int groups = P.n_groups > 0 ? P.n_groups : 1;
-    const bool long_round = groups > kFailFastShort;
-    const int n_rounds = (groups + kFailFastLong - 1) / kFailFastLong;
-    const int ff_round = tuning().ff_round > 0 ? tuning().ff_round
-                         : long_round          ? (groups + n_rounds - 1) / n_rounds
-                                               : kFailFastRound;
+    const FailFastRound ff = fail_fast_round(groups, P.kg, numel, dtype);
+    const int ff_round = tuning().ff_round > 0 ? tuning().ff_round : ff.groups;
     if (blocks_total <= 0) {
         blocks_total = resident_blocks > 0 ? resident_blocks : 2048;
-        if (serial_groups && long_round) blocks_total *= 2;
+        if (serial_groups) blocks_total *= ff.sets;
     }
     P.ff_round = ff_round < groups ? ff_round : groups;
     uint64_t C;
     if (serial_groups) {
-        C = align_up(((uint64_t)blocks_total + P.ff_round - 1) / P.ff_round, 8);
+        C = (uint64_t)blocks_total / P.ff_round / 8 * 8;
         if (C > c_ws) C = c_ws;
     } else {
         C = align_up(((uint64_t)blocks_total + groups - 1) / groups, 8);

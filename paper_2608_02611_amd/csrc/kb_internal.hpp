@@ -99,13 +99,6 @@ inline bool use_wide_kernel(int dtype, int kg, bool fail_fast, uint64_t numel, b
 // positions) resident per CU (occupancy query, cached), or 0 on failure.
 int screen_blocks_per_cu(int dtype, int kg, bool fail_fast, bool wide = false, bool loc = false);
 
-// Candidate groups per round of a fail-fast launch (see make_plan): rounds of
-// kFailFastRound up to kFailFastShort groups, equal ones of at most
-// kFailFastLong beyond.
-constexpr int kFailFastRound = 2;
-constexpr int kFailFastShort = 4;
-constexpr int kFailFastLong = 8;
-
 // Launch tables of up to this many candidates travel in the kernel
 // arguments; larger ones are read from the caller's pinned host memory.
 constexpr int kInlineCands = 128;

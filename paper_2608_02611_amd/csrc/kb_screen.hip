@@ -1347,14 +1347,20 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
 // L2.
 // FF = false: one persistent round over all groups.
 // FF = true: the groups are taken in rounds of p.ff_round groups, each round
-// over all stripes, and the grid is sized so that a round fills the device.
+// over all stripes, and the grid is sized so that a round is one or two sets
+// of resident work-groups (see fail_fast_round).
 // Work-groups are dispatched in id order, so the device works through the
 // rounds one after another; the work-groups of a group whose candidates are
 // already known to have failed leave at their first poll, and the
 // dispatcher fills their place with the next ones.  (With one persistent
 // round the work-groups of failed groups would idle while those of the live
-// ones did all their work.)  Fewer groups per round re-read the reference
-// once more per round; more groups per round balance less well.
+// ones did all their work.)
+// The order of a stripe's groups turns by one place for every 32 work-groups
+// of an XCD: its 32 CUs are filled one work-group each in turn, so with 2, 4
+// or 8 groups per round every CU would hold work-groups of one group only,
+// and the CUs of a failed group would stand idle beside those of a live one
+// (31 x 2^24 bf16, 13 of them failing: 195 us without the turn, 160 with it,
+// in one round of 8; 64 x 2^24: 338, 278; none failing: no difference).
 // WIDE: the same kernel built for 5 waves per SIMD instead of 4 (only fp32
 // with 4 candidates per group, plain launches on large tensors; see
 // use_wide_kernel).  LOC: the variant that also finds the positions.
@@ -1371,7 +1377,10 @@ __global__ __launch_bounds__(kThreads, WIDE ? 5 : min_waves(DT, KG)) void screen
     }
     const int xcd = id & 7;
     const int slot = id >> 3;
-    screen_part<DT, KG, FF, LOC>(p, tab, g0 + slot % R, (slot / R) * 8 + xcd);
+    const int s = slot / R;
+    int g = slot - s * R;
+    if constexpr (FF) g = (g + (s * R >> 5)) % R;
+    screen_part<DT, KG, FF, LOC>(p, tab, g0 + g, s * 8 + xcd);
 }
 
 __global__ void records_only_kernel(const CandEntry* uploaded, InlineTable tab, int table_inline,

@@ -344,3 +344,42 @@ def test_rounds_of_groups(dev, K):
                 assert same_record(g, f), (k, g, f)
             else:
                 check_partial(g, o, "rounds K=%d cand %d" % (K, k))
+
+
+@pytest.mark.parametrize("dt,K,n", [("f32", 33, (1 << 20) + 77),   # up to 16 MiB: equal rounds (5 + 4 groups), one set
+                                    ("f32", 17, (1 << 22) + 513),  # to 32 MiB: one round of 5, two sets
+                                    ("f32", 21, (1 << 23) + 77),   # beyond: rounds of 4 and 2, two sets
+                                    ("f16", 19, (1 << 23) + 77),   # 16-bit groups of 4 above 16 MiB: rounds of 2
+                                    ("bf16", 33, (1 << 23) + 77),  # groups of 8, the last of one candidate
+                                    ("bf16", 16, 1 << 22)])        # four groups: rounds of 2
+def test_rounds_by_size(dev, dt, K, n):
+    """The rounds of a fail-fast launch by tensor size, type and number of
+    groups: failing candidates fill whole groups, parts of groups and the
+    last; every stripe of every live group must be screened exactly once."""
+    say("fail-fast rounds by size", dt, K, n)
+    tt = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[dt]
+    atol, rtol = (ATOL, RTOL) if dt == "f32" else (1e-3, 1e-2)
+    g = torch.Generator(device=dev).manual_seed(n + K)
+    ref = (torch.randn(n, generator=g, device=dev) + 2.0).to(tt)
+    cands = []
+    for k in range(K):
+        c = ref.clone()
+        i = torch.randint(0, n, (1000,), generator=g, device=dev)
+        c[i] = (c[i].float() * (1.0 + 2.0 ** -24)).to(tt)
+        if 4 <= k < 12 or k % 5 == 3 or k == K - 1:
+            if k % 2:
+                c[torch.randint(0, n, (2,), generator=g, device=dev)] += 1.0
+            else:
+                c += 1.0
+        cands.append(c)
+    full, fsum = kb.screen(ref, cands, atol, rtol, 0)
+    orc = oracle_records(ref, cands, atol, rtol, 0)
+    assert_records_match(full, orc, "rounds by size, full")
+    for _ in range(2):
+        fast, ssum = kb.screen(ref, cands, atol, rtol, FF)
+        assert ssum == fsum, (ssum, fsum)
+        for k, (gr, f, o) in enumerate(zip(fast, full, orc)):
+            if o["mismatches"] == 0:
+                assert same_record(gr, f), (k, gr, f)
+            else:
+                check_partial(gr, o, "rounds by size %s K=%d n=%d cand %d" % (dt, K, n, k))
