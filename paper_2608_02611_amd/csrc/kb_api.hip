@@ -199,24 +199,38 @@ int plan_group_size(int n_cands, uint64_t numel, int dtype, bool fail_fast) {
     // few chunks at most, so the time is that of the kernel's code run about
     // once -- the chain through all candidates of the group and the fetch of
     // instructions that nothing has brought in yet -- and a kernel of 4 or 8
-    // candidates has that many times the code.  Below the stated bytes of all
-    // candidates, groups of 1 or 2 (us; groups of 4 or 8 -> 2 -> 1):
+    // candidates has that many times the code.  Limits by the bytes of all
+    // candidates, from 3975 shapes (1 to 300 candidates, 0.1 to 80 MiB, every
+    // type, plain and with positions): none is slower than in groups of 4 or
+    // 8 by more than the runs differ.  us in groups of 4 or 8 -> 2 -> 1:
     //   4 x 65536 fp32 12.4 -> 9.2 -> 7.8; 64 x 65536 fp16 20.4 -> 11.8 -> 10.3;
     //   16 x 262016 fp32 (16 MiB) 19.7 -> 14.7 -> 11.9;
-    //   64 x 131072 fp32 (32 MiB) 15.9 -> 13.9 -> 17.1;
-    //   16 x 2^20 fp32 (64 MiB) 19.4 -> 17.9 -> 19.1;
-    //   64 x 2^20 fp16 (128 MiB) 34.7 -> 35.7 -> 52.7;
+    //   24 x 262144 fp32 (24 MiB) 15.5 -> 14.0 -> 13.5, with positions 18.9 -> 17.2 -> 16.4,
+    //   but 100 x 131072 fp16 (25 MiB) 26.0 -> 18.2 -> 19.3;
+    //   31 x 2^19 fp32 (64 MiB) 19.0 -> 19.1 -> 19.7;
+    //   31 x 2^20 fp16 (64 MiB) 21.5 -> 23.6 -> 24.3, where 16-bit groups of 4
+    //   need fewer passes over the reference; in place of groups of 8
+    //   64 x 2^19 fp16 (64 MiB) 24.5 -> 24.1 -> 25.8;
     // fail-fast, whose rounds hold few groups: 64 x 65536 fp16 20.7 -> 11.9 ->
     //   11.1; 16 x 2^19 fp16 (16 MiB) 16.3 -> 15.1 -> 18.8; 16 x 2^20 fp16
-    //   (32 MiB) 20.1 -> 25.5 -> 29.1;
-    const uint64_t limit1 = fail_fast ? 8u << 20 : 16u << 20, limit2 = fail_fast ? 16u << 20 : 64u << 20;
+    //   (32 MiB) 20.1 -> 25.5 -> 29.1.
+    // Each group takes at least 8 work-groups and the device holds 1024 or
+    // 1280, so lists of more than 128 take no groups of 1 and lists of more
+    // than 256 none of 2 (1024 x 4096 fp32 32 us in groups of 4, 60 in groups
+    // of 1; 200 x 4096 16.7 in groups of 2, 19.0 of 1); in between
+    //   200 x 32768 fp16 (12 MiB) 29.1 in groups of 8, 20.4 of 2;
+    //   256 x 65536 fp32 (64 MiB) 23.2 in groups of 4, 25.8 of 2;
+    //   256 x 98304 fp16 (48 MiB) 31.6 in groups of 8, 28.9 of 2, 25.2 of 4.
     const uint64_t one = (uint64_t)n_cands * elem_size(dtype);  // bytes of one element of every candidate
-    // and at most 128 groups, since each takes at least 8 work-groups and
-    // the device holds 1024 (1024 x 4096 fp32 32 us in groups of 4, 60 in
-    // groups of 1; 200 x 4096 16.7 in groups of 2, 19.0 in groups of 1).
-    constexpr int kSmallGroups = 128;
-    if (n_cands <= kSmallGroups && numel <= limit1 / one) return group_size(n_cands, 1);
-    if (n_cands <= 2 * kSmallGroups && numel <= limit2 / one) return group_size(n_cands, 2);
+    const auto within = [&](uint64_t mib) { return numel <= (mib << 20) / one; };
+    const bool fp32 = dtype == DT_F32;
+    if (n_cands <= 128) {
+        if (within(fail_fast ? 8 : 16)) return group_size(n_cands, 1);
+        if (within(fail_fast ? 16 : fp32 || n_cands >= 32 ? 64 : 48)) return group_size(n_cands, 2);
+    } else if (n_cands <= 256) {
+        if (within(fail_fast ? 16 : 24)) return group_size(n_cands, 2);
+        if (!fail_fast && within(64)) return group_size(n_cands, 4);
+    }
     return long_group_size(n_cands, dtype);
 }
 
@@ -283,7 +297,9 @@ bool make_plan(int n_cands, int n_acc, uint64_t numel, int dtype, int resident_b
     //    device at once (occupancy of the chosen kernel x CUs), spread over
     //    the candidate groups -- the grid is persistent, each wave strides
     //    over the chunks -- unless a tuning override sets the total; at most
-    //    about 4096 work-groups in all;
+    //    about 4096 work-groups in all.  Rounded down: work-groups past the
+    //    resident ones would be a second round by themselves (20 x 416809
+    //    fp32 in 10 groups of 2: 17.5 us with 136 stripes, 14.8 with 128);
     //  - fail-fast launch (serial_groups): see fail_fast_round;
     //  - the workspace is laid out for the bound C_ws, independent of the
     //    device, and the launch never exceeds it.
@@ -314,7 +330,7 @@ bool make_plan(int n_cands, int n_acc, uint64_t numel, int dtype, int resident_b
         C = (uint64_t)blocks_total / P.ff_round / 8 * 8;
         if (C > c_ws) C = c_ws;
     } else {
-        C = align_up(((uint64_t)blocks_total + groups - 1) / groups, 8);
+        C = (uint64_t)blocks_total / groups / 8 * 8;
         if (C > c_plain) C = c_plain;
     }
     if (C < min_c) C = min_c;

@@ -297,6 +297,34 @@ def test_workspace_grows_with_numel(L, dt):
                 assert b <= most + 12 * 256, (K, n, b, most)
 
 
+def test_one_round_of_work_groups(L):
+    """A plain launch never exceeds one round of resident work-groups (2048
+    where the device is not known) unless every group is at its minimum of 8,
+    for any number of groups: a few more would be a second round."""
+    for dt in (kb.KB_F32, kb.KB_F16):
+        for K in (3, 5, 6, 7, 9, 11, 12, 20, 24, 28, 40, 48, 56, 100, 130, 200, 300, 1000):
+            for n in (1 << 18, 1 << 20, 1 << 24, 1 << 28):
+                plan = kb.kb_screen_launch(K, n, dt)
+                assert plan["grid"] <= max(2048, 8 * plan["n_groups"]), (K, n, plan)
+
+
+@pytest.mark.parametrize("dt,K,mib,size", [
+    ("F32", 128, 16, 1), ("F32", 31, 64, 2), ("F16", 31, 48, 2), ("BF16", 32, 64, 2), ("F16", 128, 64, 2),
+    ("F32", 129, 24, 2), ("F16", 256, 24, 2), ("F16", 129, 64, 4), ("BF16", 256, 64, 4)])
+def test_group_size_by_bytes(L, dt, K, mib, size):
+    """The group size up to and past each limit in bytes of all candidates."""
+    code, es = getattr(kb, "KB_" + dt), 4 if dt == "F32" else 2
+    n = (mib << 20) // (K * es)
+    past = kb.kb_screen_launch(K, n + 1, code)["group_size"]
+    assert kb.kb_screen_launch(K, n, code)["group_size"] == size
+    if size == 1:
+        assert past == 2
+    elif size == 2 and K > 128 and dt != "F32":
+        assert past == 4
+    else:
+        assert past == (8 if K >= 32 and dt != "F32" else 4)
+
+
 @pytest.mark.parametrize("n", [1, 4096, 16384, 65536])
 def test_small_groups_only_for_short_lists(L, n):
     """A group takes at least 8 work-groups: lists of more than 128 (256)

@@ -2,8 +2,10 @@
 between them (GPU), against the oracle.
 
 The plan groups candidates by the bytes of all of them together: groups of 1
-up to 16 MiB (8 MiB fail-fast), of 2 up to 64 MiB (16 MiB fail-fast), else of
-4, or 8 for 32 or more 16-bit candidates.
+up to 16 MiB (8 MiB fail-fast), of 2 up to 64 MiB (48 MiB for up to 31 16-bit
+candidates, 16 MiB fail-fast), else of 4, or 8 for 32 or more 16-bit
+candidates; lists of more than 128 candidates groups of 2 up to 24 MiB and 4 up
+to 64 MiB.
 """
 import sys
 
@@ -110,3 +112,24 @@ def test_one_workspace_for_all_sizes(dev, dt, K):
         assert_records_match(kb.kb_screen_stats(st, K)[0], orc, "positions")
         assert kb.read_locate(d_loc, K) == locs
     assert len(seen) >= 3, seen
+
+
+@pytest.mark.parametrize("dt,K,mib", [("f32", 131, 24), ("f16", 131, 24), ("bf16", 131, 64), ("bf16", 31, 48)])
+@pytest.mark.parametrize("past", [0, 1])
+def test_long_lists_at_the_limits(dev, dt, K, mib, past):
+    """Lists of more than 128 candidates (their table in host memory) and the
+    16-bit limit of short lists, up to and past each limit."""
+    n = mib * MIB // (K * (4 if dt == "f32" else 2)) + past
+    atol, rtol = (1e-5, 1e-3) if dt == "f32" else (1e-3, 1e-2)
+    print("long list", dt, K, n, flush=True)
+    r, cs = tensors(dt, K, n)
+    orc = oracle_records(r, cs, atol, rtol, dt=dt)
+    locs = oracle_positions_host(r, cs, dt, atol, rtol, orc)
+    ref, cands = to_device(r, dt, dev), [to_device(c, dt, dev) for c in cs]
+    ws = kb.alloc_workspace(K, n, CODE[dt], dev, positions=True)
+    st, _ = kb.kb_screen(ref, cands, atol, rtol, 0, ws)
+    assert_records_match(kb.kb_screen_stats(st, K)[0], orc, "plain")
+    d_loc = kb.alloc_locate(K, dev)
+    st, _ = kb.kb_screen(ref, cands, atol, rtol, 0, ws, d_loc=d_loc)
+    assert_records_match(kb.kb_screen_stats(st, K)[0], orc, "positions")
+    assert kb.read_locate(d_loc, K) == locs
