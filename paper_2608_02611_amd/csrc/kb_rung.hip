@@ -7,14 +7,15 @@
 // over the baseline (Appendix A.5), the quantiles behind the tail ratios of
 // Table A.3, and per candidate the latency and the runtime score of Eq. 2.
 //
-// rung_kernel        rows of at most 256 samples (every rung of the paper) on
-//                    at most 64 shapes: one work-group per candidate, one
-//                    wave per row, up to 4 samples per lane, a bitonic sort
-//                    across lanes and registers, then the candidate's score;
-// rows_block_kernel  longer rows (up to kRungMaxIter) or more shapes: one
-//                    work-group per row, bitonic sort in LDS;
-// scores_kernel      after those, one thread per candidate: latency, score,
-//                    speedups;
+// rung_kernel        rows of at most 256 samples (every rung of the paper):
+//                    one work-group per candidate, one wave per row, up to 4
+//                    samples per lane, a bitonic sort across lanes and
+//                    registers, then the candidate's score (or rows only);
+// rows_block_kernel  longer rows (up to kRungMaxIter), and rows of more than
+//                    128 samples where there are few: one work-group per row,
+//                    bitonic sort in LDS;
+// scores_kernel      after rows alone, one thread per candidate: latency,
+//                    score, speedups (which way is taken: launch_rung_stats);
 // promote_kernel     the promotion decision over the scores.
 //
 // Every sum runs left to right in binary64, as the definitions read (the
@@ -134,122 +135,139 @@ __device__ __forceinline__ bool load_row(const double* t, int n, int lane, doubl
     return __builtin_amdgcn_ballot_w64(bad) == 0;
 }
 
-// Sums of two rows, each left to right over its samples (two independent
-// chains, so the second costs no time).  The loop runs to a multiple of 4:
-// adding zero leaves a positive sum as it is.
-template <int E>
+// Sum of a row left to right over its samples, and with BOTH of a second one
+// (two independent chains).  The loop runs to a multiple of 4: adding zero
+// leaves a positive sum as it is.
+template <int E, bool BOTH>
 __device__ __forceinline__ void row_sums(const double a[E], const double b[E], int n, int lane, double& sa, double& sb) {
     sa = 0.0;
     sb = 0.0;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const bool in = 64 * e + lane < n;
-        const double x = in ? a[e] : 0.0, y = in ? b[e] : 0.0;
+        const double x = in ? a[e] : 0.0, y = BOTH && in ? b[e] : 0.0;
         const int m = min(64, n - 64 * e);
         for (int i = 0; i < m; i += 4) {
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 sa = __dadd_rn(sa, readlane_f64(x, i + u));
-                sb = __dadd_rn(sb, readlane_f64(y, i + u));
+                if constexpr (BOTH) sb = __dadd_rn(sb, readlane_f64(y, i + u));
             }
         }
     }
 }
 
-// Rows of at most 64 E samples on at most kFusedShapes shapes: one work-group
-// per candidate, one wave per row (striding over the shapes), then the
-// candidate's score.  The wave also sums the baseline's row of its shape, so
-// the speedups and the score need nothing from another work-group and the
-// whole of kb_rung_stats is one launch.  The kernel is a chain of latencies
-// (a few thousand waves of some 500 instructions): the sort's steps are DPP
-// permutations instead of LDS permutes where they stay inside 16 lanes, and
-// the quantiles, the quotients and the stores of a row are one each, spread
-// over the lanes.
+// Rows of at most 64 E samples: a work-group per candidate, a wave per row
+// (striding over the shapes), then the candidate's score.  A wave also sums
+// the baseline's row of its shape, beside its own for the work-group's first
+// candidate, so the speedups and the score need nothing from another
+// work-group and the whole of kb_rung_stats is one launch.  The kernel is a
+// chain of latencies (a few thousand waves of some 500 instructions): the
+// sort's steps are DPP permutations instead of LDS permutes where they stay
+// inside 16 lanes, and the quantiles, the quotients and the stores of a row
+// are one each, spread over the lanes.
 // 1024 candidates x 3 shapes x 60 samples: rows and scores apart 7.4 + 6.2 us
 // and a launch, this kernel 9.5 us; the promotion's batched loads 8.5 -> 5.9.
-constexpr int kFusedShapes = 64;
-constexpr int kWaveSamples = 4;  // samples per lane at most
+// With scores NULL only the rows are formed.
+constexpr int kFusedShapes = 4096;      // 64 KB of LDS
+constexpr int kFusedWaves = 16;         // waves of a work-group at most
+constexpr int kFusedCandidates = 8192;  // (see launch_rung_stats)
+constexpr int kWaveSamples = 4;         // samples per lane at most
 
 template <int E>
-__global__ __launch_bounds__(kThreads) void rung_kernel(RungParams p, const double* __restrict__ samples,
-                                                        kb_sample_stats* __restrict__ rows,
-                                                        kb_rung_score* __restrict__ scores) {
-    __shared__ double s_mean[2][kFusedShapes];  // own, baseline
-    __shared__ int s_valid[2][kFusedShapes];
+__global__ __launch_bounds__(64 * kFusedWaves) void rung_kernel(RungParams p, const double* __restrict__ samples,
+                                                                kb_sample_stats* __restrict__ rows,
+                                                                kb_rung_score* __restrict__ scores) {
+    extern __shared__ double s_mean[];  // [2][n_shapes]: own, baseline; NaN where the row is invalid (a sum of
+                                        // positive samples never is)
     const int lane = threadIdx.x & 63;
-    const int n = p.n_iter, S = p.n_shapes, c = blockIdx.x;
+    const int n = p.n_iter, S = p.n_shapes;
+    double* const s_base = s_mean + S;
     const double nan = __builtin_nan("");
-    for (int s = threadIdx.x >> 6; s < S; s += blockDim.x >> 6) {
-        const size_t row = (size_t)c * S + s;
-        double v[E], b[E];
-        const bool valid = load_row<E>(samples + row * (size_t)n, n, lane, v);
-        // (no baseline: its own row again, not used)
-        const size_t base_row = p.base >= 0 ? (size_t)p.base * S + s : row;
-        const bool base_valid = load_row<E>(samples + base_row * (size_t)n, n, lane, b) && p.base >= 0;
-        double sum, base_sum;
-        row_sums<E>(v, b, n, lane, sum, base_sum);
-        uint64_t x[E];
+    for (int c = blockIdx.x; c < p.n_cands; c += gridDim.x) {
+        const bool first = c == (int)blockIdx.x;
+        for (int s = threadIdx.x >> 6; s < S; s += blockDim.x >> 6) {
+            const size_t row = (size_t)c * S + s;
+            double v[E];
+            const bool valid = load_row<E>(samples + row * (size_t)n, n, lane, v);
+            double sum, base_sum = 0.0;
+            bool base_valid = false;
+            if (first && p.base >= 0) {
+                double b[E];
+                base_valid = load_row<E>(samples + ((size_t)p.base * S + s) * (size_t)n, n, lane, b);
+                row_sums<E, true>(v, b, n, lane, sum, base_sum);
+            } else {
+                row_sums<E, false>(v, v, n, lane, sum, base_sum);
+            }
+            uint64_t x[E];
 #pragma unroll
-        for (int e = 0; e < E; ++e) x[e] = __builtin_bit_cast(uint64_t, v[e]);
-        wave_sort<E>(x, lane);
-        // Lane w forms word w of the record: the mean (0), the quantiles
-        // (1-4), their ratios to the median (5-7), the speedup (8; first the
-        // baseline's mean).  The p-quantile of the sorted samples: linear
-        // interpolation between the order statistics around h = (n - 1) p.
-        const double q_p = lane == 1 ? 0.5 : lane == 2 || lane == 5 ? 0.9 : lane == 3 || lane == 6 ? 0.95 : 0.99;
-        const double h = __dmul_rn((double)(n - 1), q_p);
-        const int k = (int)floor(h);
-        const int ka = min(k, n - 1), kb = min(k + 1, n - 1);
-        uint64_t xa = __shfl((unsigned long long)x[0], ka & 63, 64), xb = __shfl((unsigned long long)x[0], kb & 63, 64);
+            for (int e = 0; e < E; ++e) x[e] = __builtin_bit_cast(uint64_t, v[e]);
+            wave_sort<E>(x, lane);
+            // Lane w forms word w of the record: the mean (0), the quantiles
+            // (1-4), their ratios to the median (5-7), the speedup (8; first the
+            // baseline's mean).  The p-quantile of the sorted samples: linear
+            // interpolation between the order statistics around h = (n - 1) p.
+            const double q_p = lane == 1 ? 0.5 : lane == 2 || lane == 5 ? 0.9 : lane == 3 || lane == 6 ? 0.95 : 0.99;
+            const double h = __dmul_rn((double)(n - 1), q_p);
+            const int k = (int)floor(h);
+            const int ka = min(k, n - 1), kb = min(k + 1, n - 1);
+            uint64_t xa = __shfl((unsigned long long)x[0], ka & 63, 64);
+            uint64_t xb = __shfl((unsigned long long)x[0], kb & 63, 64);
 #pragma unroll
-        for (int e = 1; e < E; ++e) {
-            const uint64_t ya = __shfl((unsigned long long)x[e], ka & 63, 64);
-            const uint64_t yb = __shfl((unsigned long long)x[e], kb & 63, 64);
-            if (ka >> 6 == e) xa = ya;
-            if (kb >> 6 == e) xb = yb;
+            for (int e = 1; e < E; ++e) {
+                const uint64_t ya = __shfl((unsigned long long)x[e], ka & 63, 64);
+                const uint64_t yb = __shfl((unsigned long long)x[e], kb & 63, 64);
+                if (ka >> 6 == e) xa = ya;
+                if (kb >> 6 == e) xb = yb;
+            }
+            const double fa = __builtin_bit_cast(double, xa), fb = __builtin_bit_cast(double, xb);
+            double q = fa;
+            if (k < n - 1) q = __dadd_rn(fa, __dmul_rn(__dsub_rn(h, (double)k), __dsub_rn(fb, fa)));
+            const double q50 = readlane_f64(q, 1);
+            const double num = lane == 0 ? sum : lane == 8 ? base_sum : q;
+            const double quot = num / (lane == 0 || lane == 8 ? (double)n : q50);
+            const double mean = readlane_f64(quot, 0);
+            double base_mean = nan;
+            if (p.base >= 0) base_mean = !first ? s_base[s] : base_valid ? readlane_f64(quot, 8) : nan;
+            double word = lane >= 1 && lane <= 4 ? q : quot;
+            if (lane == 8) word = base_mean / mean;
+            if (!valid) word = nan;
+            if (lane == 9)
+                word = __builtin_bit_cast(double, ((uint64_t)(valid ? 1u : 0u) << 32) | (uint32_t)n);
+            if (lane < 10) ((double*)&rows[row])[lane] = word;
+            if (lane == 0) {
+                s_mean[s] = valid ? mean : nan;
+                if (first) s_base[s] = base_mean;
+            }
         }
-        const double fa = __builtin_bit_cast(double, xa), fb = __builtin_bit_cast(double, xb);
-        double q = fa;
-        if (k < n - 1) q = __dadd_rn(fa, __dmul_rn(__dsub_rn(h, (double)k), __dsub_rn(fb, fa)));
-        const double q50 = readlane_f64(q, 1);
-        const double num = lane == 0 ? sum : lane == 8 ? base_sum : q;
-        const double quot = num / (lane == 0 || lane == 8 ? (double)n : q50);
-        const double mean = readlane_f64(quot, 0);
-        const double base_mean = base_valid ? readlane_f64(quot, 8) : nan;
-        double word = lane >= 1 && lane <= 4 ? q : quot;
-        if (lane == 8) word = base_mean / mean;
-        if (!valid) word = nan;
-        if (lane == 9)
-            word = __builtin_bit_cast(double, ((uint64_t)(valid ? 1u : 0u) << 32) | (uint32_t)n);
-        if (lane < 10) ((double*)&rows[row])[lane] = word;
-        if (lane == 0) {
-            s_mean[0][s] = valid ? mean : nan;
-            s_valid[0][s] = valid ? 1 : 0;
-            s_mean[1][s] = base_mean;
-            s_valid[1][s] = base_valid ? 1 : 0;
+        if (scores == nullptr) continue;
+        __syncthreads();
+        if (threadIdx.x < 64) {
+            // lane 0: the candidate, lane 1: the baseline.  Latency: the mean of
+            // the row means, left to right; NaN if a row is invalid.
+            const double* means = lane & 1 ? s_base : s_mean;
+            double lat = 0.0;
+            bool ok = true;
+            for (int s = 0; s < S; ++s) {
+                const double m = means[s];
+                lat = __dadd_rn(lat, m);
+                ok &= m == m;
+            }
+            lat = ok ? lat / (double)S : nan;
+            const bool own_ok = __builtin_amdgcn_readlane(ok ? 1 : 0, 0) != 0;
+            const double own = readlane_f64(lat, 0), base = readlane_f64(lat, 1);
+            // word 1: Eq. 2, the latency term plus the one rung term gamma(r) = alpha r + beta b_r; word 2: the
+            // speedup
+            double word = (lane == 1 ? 1e6 : base) / (lane == 1 ? (own > 1.0 ? own : 1.0) : own);
+            if (lane == 1)
+                word = __dadd_rn(word, __dadd_rn(__dmul_rn(p.alpha, (double)p.rung), __dmul_rn(p.beta, p.budget)));
+            if (!own_ok) word = lane == 1 ? -__builtin_inf() : nan;
+            if (lane == 0) word = own;
+            if (lane == 3) word = __builtin_bit_cast(double, (uint64_t)(own_ok ? 1u : 0u));
+            if (lane < 4) ((double*)&scores[c])[lane] = word;
         }
+        __syncthreads();
     }
-    __syncthreads();
-    if (threadIdx.x >= 64) return;
-    // lane 0: the candidate, lane 1: the baseline.  Latency: the mean of the
-    // row means, left to right; NaN if a row is invalid.
-    const int who = lane & 1;
-    double lat = 0.0;
-    int ok = 1;
-    for (int s = 0; s < S; ++s) {
-        lat = __dadd_rn(lat, s_mean[who][s]);
-        ok &= s_valid[who][s];
-    }
-    lat = ok ? lat / (double)S : nan;
-    const bool own_ok = __builtin_amdgcn_readlane(ok, 0) != 0;
-    const double own = readlane_f64(lat, 0), base = readlane_f64(lat, 1);
-    // word 1: Eq. 2, the latency term plus the one rung term gamma(r) = alpha r + beta b_r; word 2: the speedup
-    double word = (lane == 1 ? 1e6 : base) / (lane == 1 ? (own > 1.0 ? own : 1.0) : own);
-    if (lane == 1) word = __dadd_rn(word, __dadd_rn(__dmul_rn(p.alpha, (double)p.rung), __dmul_rn(p.beta, p.budget)));
-    if (!own_ok) word = lane == 1 ? -__builtin_inf() : nan;
-    if (lane == 0) word = own;
-    if (lane == 3) word = __builtin_bit_cast(double, (uint64_t)(own_ok ? 1u : 0u));
-    if (lane < 4) ((double*)&scores[c])[lane] = word;
 }
 
 // One work-group per row of up to kRungMaxIter samples, sorted in LDS.
@@ -431,21 +449,77 @@ hipError_t launch_rung_promote(const kb_rung_score* scores, int n, int base, int
     return hipGetLastError();
 }
 
+// Waves per work-group of rung_kernel: one per shape if the device (8192
+// waves) has room for them, at least 4, at most 16, and the rows spread evenly.
+// (us: 64 candidates x 16 shapes x 60 samples 16.0 with 4 waves, 10.4 with 16;
+// 5000 x 17 x 60 135 with 4, 152 with 8, 195 with 16.)
+int rung_waves(const RungParams& p, int* rows_per_wave) {
+    const int room = 8192 / p.n_cands;
+    const int most = room < 4 ? 4 : room > kFusedWaves ? kFusedWaves : room;
+    *rows_per_wave = (p.n_shapes + most - 1) / most;
+    return (p.n_shapes + *rows_per_wave - 1) / *rows_per_wave;
+}
+
+hipError_t launch_rung_kernel(const RungParams& p, const double* samples, kb_sample_stats* rows,
+                              kb_rung_score* scores, hipStream_t stream) {
+    int per_wave;
+    const int waves = rung_waves(p, &per_wave);
+    // two candidates per work-group once that leaves the device full: the
+    // baseline is then summed for every other candidate (8000 x 4 x 60 50 us
+    // with one, 44 with two, 43 with four, 46 with eight)
+    const int each = (int64_t)p.n_cands * waves >= 16384 ? 2 : 1;
+    const dim3 grid((p.n_cands + each - 1) / each), block(64 * waves);
+    const size_t lds = 2 * sizeof(double) * (size_t)p.n_shapes;
+    if (p.n_iter <= 64) hipLaunchKernelGGL(rung_kernel<1>, grid, block, lds, stream, p, samples, rows, scores);
+    else if (p.n_iter <= 128) hipLaunchKernelGGL(rung_kernel<2>, grid, block, lds, stream, p, samples, rows, scores);
+    else hipLaunchKernelGGL(rung_kernel<4>, grid, block, lds, stream, p, samples, rows, scores);
+    return hipGetLastError();
+}
+
+// Rows and scores in one launch, or apart.  Measured, us (candidates x shapes x
+// samples; rung_kernel with the scores, rows by rung_kernel and scores_kernel,
+// rows_block_kernel and scores_kernel):
+//   up to 64 samples the one launch is the fastest (1 x 1 x 60 5.2, 6.7, 8.1;
+//     1 x 64 x 60 33, 44, 48; 4 x 1000 x 60 486, 666, 679; 8000 x 4 x 60 44 and
+//     46 before) except for very many candidates, where the scores take 64
+//     lanes each in it and one lane apart (16384 x 3 x 60 67, 55; 62 before);
+//   65 to 128: a row takes a wave 7 us, so few candidates with many rows per
+//     wave are better spread over the device (16 x 20 x 128 21, 26, 26;
+//     1 x 48 x 128 48, 37, 36; but 64 x 64 x 128 64, 72, 84);
+//   129 to 256: a row takes a wave 13 us and a work-group 9 (1 x 3 x 256 15.2,
+//     18.2, 12.7; 64 x 16 x 256 34, 30, 27; 64 x 64 x 256 124, 88, 96), until
+//     there are candidates for most CUs (255 x 4 x 256 16.1, 20.1, 18.6;
+//     1024 x 3 x 200 23, 29, 36; but 512 x 2 x 256 19.8, 20.0, 16.4).
 hipError_t launch_rung_stats(const RungParams& p, const double* samples, kb_sample_stats* rows,
                              kb_rung_score* scores, hipStream_t stream) {
     const int n_rows = p.n_cands * p.n_shapes;
-    if (p.n_iter <= 64 * kWaveSamples && p.n_shapes <= kFusedShapes) {
-        const dim3 grid(p.n_cands), block(64 * (p.n_shapes < kThreads / 64 ? p.n_shapes : kThreads / 64));
-        if (p.n_iter <= 64) hipLaunchKernelGGL(rung_kernel<1>, grid, block, 0, stream, p, samples, rows, scores);
-        else if (p.n_iter <= 128) hipLaunchKernelGGL(rung_kernel<2>, grid, block, 0, stream, p, samples, rows, scores);
-        else hipLaunchKernelGGL(rung_kernel<4>, grid, block, 0, stream, p, samples, rows, scores);
-        return hipGetLastError();
+    int per_wave;
+    rung_waves(p, &per_wave);
+    const bool fits = p.n_shapes <= kFusedShapes && p.n_cands <= kFusedCandidates;
+    bool fused, by_wave;  // one launch; else rows by rung_kernel
+    if (p.n_iter <= 64) fused = fits, by_wave = true;
+    else if (p.n_iter <= 128) fused = fits && (per_wave <= 2 || p.n_cands >= 64), by_wave = true;
+    else {
+        fused = fits && p.n_iter <= 64 * kWaveSamples && p.n_cands >= 192 && n_rows >= (p.n_shapes >= 3 ? 768 : 1200);
+        by_wave = p.n_iter <= 64 * kWaveSamples && n_rows >= 4096;
     }
-    int P = 1;
-    while (P < p.n_iter) P <<= 1;
-    hipLaunchKernelGGL(rows_block_kernel, dim3(n_rows), dim3(kThreads), 0, stream, samples, p.n_iter, P, rows);
-    hipError_t e = hipGetLastError();
+    if (fused) return launch_rung_kernel(p, samples, rows, scores, stream);
+    hipError_t e;
+    if (by_wave) {
+        // every row a candidate of one shape without a baseline
+        RungParams q = p;
+        q.n_cands = n_rows;
+        q.n_shapes = 1;
+        q.base = -1;
+        e = launch_rung_kernel(q, samples, rows, nullptr, stream);
+    } else {
+        int P = 1;
+        while (P < p.n_iter) P <<= 1;
+        hipLaunchKernelGGL(rows_block_kernel, dim3(n_rows), dim3(kThreads), 0, stream, samples, p.n_iter, P, rows);
+        e = hipGetLastError();
+    }
     if (e != hipSuccess) return e;
+    // (sets the rows' speedups too)
     hipLaunchKernelGGL(scores_kernel, dim3((p.n_cands + kThreads - 1) / kThreads), dim3(kThreads), 0,
                        stream, p, rows, scores);
     return hipGetLastError();

@@ -135,3 +135,23 @@ def test_fused_kernel_edges(dev, n_iter, S):
     t[0, S - 1, n_iter - 1] = np.nan
     for base in (0, 1):
         check(t, dev, base=base, rung=1, budget=16.0, label="n=%d S=%d invalid, base=%d" % (n_iter, S, base))
+
+
+@pytest.mark.parametrize("C,S,n_iter", [
+    (2, 17, 60), (600, 9, 64), (3, 70, 64), (1, 300, 5), (1, 4096, 2), (1, 4097, 2),  # waves striding over shapes; too many shapes
+    (8190, 3, 3), (8193, 2, 3), (8193, 1, 64), (16384, 1, 5),           # two candidates per work-group; rows apart
+    (3, 32, 100), (3, 33, 100), (64, 33, 128), (63, 49, 128),           # 65 .. 128 samples: one launch, or rows apart
+    (255, 3, 129), (192, 4, 129), (256, 2, 256), (600, 2, 256),         # 129 .. 256: by work-group or by wave
+    (64, 64, 130), (63, 64, 256)])
+def test_ways_of_the_launch(dev, C, S, n_iter):
+    """Every way kb_rung_stats may take, by candidates, shapes and samples:
+    rows and scores in one launch (with 1 to 16 waves, one or two candidates
+    per work-group) or apart, with a baseline, none, and invalid rows."""
+    say("rung ways", C, S, n_iter)
+    t = synth.timing_samples(C, min(S, 16), n_iter, seed=C + S + n_iter).numpy()
+    t = np.ascontiguousarray(np.tile(t, (1, -(-S // t.shape[1]), 1))[:, :S])
+    t *= 1.0 + 0.001 * np.arange(S)[None, :, None]
+    check(t, dev, base=C - 1, rung=1, budget=16.0, label="C=%d S=%d n=%d" % (C, S, n_iter))
+    t[C // 2, S - 1, n_iter - 1] = np.nan
+    for base in (C // 2, -1):
+        check(t, dev, base=base, rung=1, budget=16.0, label="C=%d S=%d n=%d invalid, base=%d" % (C, S, n_iter, base))
