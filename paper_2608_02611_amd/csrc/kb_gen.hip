@@ -455,14 +455,14 @@ __device__ __forceinline__ uint32_t perturb_block(uint32_t bits, u32x4 w, float 
 template <int DT>
 constexpr int kVec = DT == DT_F32 ? 4 : 8;  // elements of 16 bytes
 
-// The changed bits of elements g0 .. g0 + kVec - 1 (g0 a multiple of 4 for
-// ops 1-5), in place.
-template <int DT, int OP>
-__device__ __forceinline__ void perturb_vec(uint32_t e[kVec<DT>], uint64_t g0, float a, float b, float p, uint32_t k0,
+// The changed bits of elements g0 .. g0 + V - 1 (g0 a multiple of 4 for ops
+// 1-5), in place.
+template <int DT, int OP, int V>
+__device__ __forceinline__ void perturb_vec(uint32_t e[V], uint64_t g0, float a, float b, float p, uint32_t k0,
                                             uint32_t k1, uint32_t stream_id, uint32_t sub) {
     if constexpr (OP <= KB_PERTURB_FLIP_LSB_WHERE) {
 #pragma unroll
-        for (int q = 0; q < kVec<DT>; q += 4) {
+        for (int q = 0; q < V; q += 4) {
             const uint64_t blk = (g0 + q) >> 2;
             const u32x4 w = philox4x32_10({(uint32_t)blk, (uint32_t)(blk >> 32), sub, stream_id}, k0, k1);
             const uint32_t u[4] = {w.x, w.y, w.z, w.w};
@@ -476,7 +476,7 @@ __device__ __forceinline__ void perturb_vec(uint32_t e[kVec<DT>], uint64_t g0, f
         }
     } else {
 #pragma unroll
-        for (int i = 0; i < kVec<DT>; ++i) {
+        for (int i = 0; i < V; ++i) {
             const uint64_t g = g0 + i;
             e[i] = perturb_block<OP>(
                 e[i], philox4x32_10({(uint32_t)g, (uint32_t)(g >> 32), sub, stream_id}, k0, k1), a, b, p);
@@ -484,27 +484,29 @@ __device__ __forceinline__ void perturb_vec(uint32_t e[kVec<DT>], uint64_t g0, f
     }
 }
 
-// Thread t takes elements lead + kVec t .. of the stream's range, where lead
-// <= 0 puts g on a multiple of 4 (ops 1-5, an offset that is none: the memory
-// accesses are then single elements); elements outside [0, n) are skipped.
-template <int DT, int OP>
+// Thread t takes elements V t - lead .. of the stream's range, where lead puts
+// g on a multiple of 4 (ops 1-5, an offset that is none: the memory accesses
+// are then single elements); elements outside [0, n) are skipped.  V: 16
+// bytes, but 4 elements where lead is not zero: eight 16-bit elements read
+// and written one by one are the longer chain (4099 fp16 scaled 4.1 us, 2.9
+// with one thread per element, 3.0 now; 16.8 million of them at an offset of 1 33 us, 41, 22 now).
+template <int DT, int OP, int V>
 __global__ __launch_bounds__(256) void perturb_kernel(void* dst, const void* src, uint64_t n, float a, float b,
                                                       float p, uint32_t k0, uint32_t k1, uint32_t stream_id,
                                                       uint32_t sub, uint64_t offset, uint32_t lead,
                                                       uint64_t n_items) {
-    constexpr int V = kVec<DT>;
-    const uint64_t n_whole = lead == 0u ? n / V : 0;
+    const uint64_t n_whole = V == kVec<DT> && lead == 0u ? n / V : 0;
     const uint64_t step = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n_items; t += step) {
         const uint64_t j0 = t * V - lead;  // (wraps below zero for t = 0, lead > 0)
         uint32_t e[V];
-        if (t < n_whole) {
+        if (V == kVec<DT> && t < n_whole) {
             const uint4 x = ((const uint4*)src)[t];
             const uint32_t q[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
             for (int i = 0; i < V; ++i)
-                e[i] = DT == DT_F32 ? q[i % 4] : (q[i / (V / 4)] >> (16 * (i & 1))) & 0xFFFFu;
-            perturb_vec<DT, OP>(e, offset + j0, a, b, p, k0, k1, stream_id, sub);
+                e[i] = DT == DT_F32 ? q[i % 4] : (q[i / 2 % 4] >> (16 * (i & 1))) & 0xFFFFu;
+            perturb_vec<DT, OP, V>(e, offset + j0, a, b, p, k0, k1, stream_id, sub);
             uint4 y;
             if constexpr (DT == DT_F32) y = make_uint4(e[0], e[1], e[2], e[3]);
             else y = make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[V - 4] | (e[V - 3] << 16), e[V - 2] | (e[V - 1] << 16));
@@ -512,7 +514,7 @@ __global__ __launch_bounds__(256) void perturb_kernel(void* dst, const void* src
         } else {
 #pragma unroll
             for (int i = 0; i < V; ++i) e[i] = j0 + i < n ? load_bits<DT>(src, j0 + i) : 0u;
-            perturb_vec<DT, OP>(e, offset + j0, a, b, p, k0, k1, stream_id, sub);
+            perturb_vec<DT, OP, V>(e, offset + j0, a, b, p, k0, k1, stream_id, sub);
 #pragma unroll
             for (int i = 0; i < V; ++i)
                 if (j0 + i < n) store_bits<DT>(dst, j0 + i, e[i]);
@@ -524,9 +526,13 @@ template <int DT, int OP>
 hipError_t launch_perturb_op(void* dst, const void* src, uint64_t n, float a, float b, float p, uint64_t seed,
                              uint32_t stream_id, uint32_t sub, uint64_t offset, hipStream_t stream) {
     const uint32_t lead = OP <= KB_PERTURB_FLIP_LSB_WHERE ? (uint32_t)(offset & 3u) : 0u;
-    const uint64_t n_items = n / kVec<DT> + (n % kVec<DT> + lead + kVec<DT> - 1) / kVec<DT>;
-    hipLaunchKernelGGL((perturb_kernel<DT, OP>), dim3(elementwise_grid(n_items)), dim3(256), 0, stream, dst, src, n,
-                       a, b, p, (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, sub, offset, lead, n_items);
+    const auto launch = [&](auto kernel, uint64_t V) {
+        const uint64_t n_items = n / V + (n % V + lead + V - 1) / V;
+        hipLaunchKernelGGL(kernel, dim3(elementwise_grid(n_items)), dim3(256), 0, stream, dst, src, n, a, b, p,
+                           (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, sub, offset, lead, n_items);
+    };
+    if (lead == 0u || kVec<DT> == 4) launch(perturb_kernel<DT, OP, kVec<DT>>, kVec<DT>);
+    else launch(perturb_kernel<DT, OP, 4>, 4);
     return hipGetLastError();
 }
 

@@ -228,6 +228,38 @@ def test_perturb_add_normal(dev, dt):
 
 
 @pytest.mark.parametrize("dt", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("n,offset", [(8, 0), (9, 4), (24, 8), (4099, 0), (4099, 12), ((1 << 20) + 3, (1 << 32) + 4),
+                                      (3, 3), (1, 2), (4099, 1), (4098, 2), (4097, 3)])
+def test_perturb_vectors_exact(dev, dt, n, offset):
+    """Offsets that are a multiple of 4 (16-byte accesses, the tail element by
+    element) and those that are not (4 elements per thread): bit-exact, in
+    place too, and nothing past the end written.  Normal noise: the same
+    bits as those elements of the whole stream."""
+    src = _src(dt, n, n + 2)
+    words = torch.int16 if dt != "f32" else torch.int32
+    d_src = to_device(src, dt, dev)
+    bits = (lambda a: a.view(np.uint32)) if dt == "f32" else (lambda a: a)
+    for op, a, b, p in EXACT_OPS:
+        want = oracle.perturb(src, dt, op, a, b, p, seed=3, stream_id=41, sub=2, offset=offset)
+        buf = torch.full((n + 16,), 7, dtype=words, device=dev)
+        out = buf[:n].view(d_src.dtype)
+        kb.kb_gen_perturb(out, d_src, op, a, b, p, seed=3, stream_id=41, sub=2, offset=offset)
+        assert np.array_equal(bits(host(out)), bits(want)), (dt, op, n, offset)
+        assert bool((buf[n:] == 7).all()), (dt, op, n, offset)
+        inplace = d_src.clone()
+        kb.kb_gen_perturb(inplace, inplace, op, a, b, p, seed=3, stream_id=41, sub=2, offset=offset)
+        assert torch.equal(inplace.view(words), out.view(words))
+    back = offset % 16 + 16
+    whole = torch.cat([torch.zeros(back, dtype=d_src.dtype, device=dev), d_src])
+    kb.kb_gen_perturb(whole, whole, kb.KB_PERTURB_ADD_NORMAL, 1e-3, seed=3, stream_id=41, sub=2,
+                      offset=offset - back if offset >= back else offset + 16 * 3 - back)
+    out = torch.empty_like(d_src)
+    kb.kb_gen_perturb(out, d_src, kb.KB_PERTURB_ADD_NORMAL, 1e-3, seed=3, stream_id=41, sub=2,
+                      offset=offset if offset >= back else offset + 16 * 3)
+    assert torch.equal(out.view(words), whole[back:].view(words)), (dt, n, offset)
+
+
+@pytest.mark.parametrize("dt", ["f32", "f16", "bf16"])
 def test_scatter(dev, dt):
     n = 70001
     src = _src(dt, n, 4)
