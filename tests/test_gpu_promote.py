@@ -66,6 +66,12 @@ def test_random_scores(dev, n):
         check(s, v, dev, base, num, den, "n=%d %d/%d base=%d" % (n, num, den, base))
 
 
+@pytest.mark.parametrize("n", [63, 64, 65, 127, 128, 129, 511, 512, 513])
+def test_batch_edges(dev, n):
+    """One, two or eight scores per lane in flight, each at its edges."""
+    test_random_scores(dev, n)
+
+
 def test_nan_scores_invalid_baseline_and_all_equal(dev):
     check(np.array([np.nan, 5.0, 7.0, 1e9, 2.0]), np.array([1, 1, 1, 0, 1], np.int32), dev, -1, 1, 1,
           "nan")
