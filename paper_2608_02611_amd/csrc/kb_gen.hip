@@ -4,11 +4,19 @@
 // block g / 4 (key = seed, counter = (lo32(b), hi32(b), sub, stream_id)),
 // mapped to a uniform value by u = (x >> 8) 2^-24 and fmaf(u, p1 - p0, p0), or
 // to a normal value by the Box-Muller transform evaluated in binary64 over the
-// word pair of g's half-block.  One thread computes one Philox block and
-// stores its (up to) four elements; interior blocks of an offset that is a
-// multiple of 4 store with one 16-byte (fp32/u32) or 8-byte (fp16/bf16)
-// write.  The work is ALU-bound (ten 32x32->64 multiply rounds per block,
-// plus binary64 log/sqrt/sincos per normal pair).
+// word pair of g's half-block.
+//
+// gen_kernel           one thread computes one Philox block and stores its (up
+//                      to) four elements; interior blocks of an offset that is
+//                      a multiple of 4 store with one 16-byte (fp32/u32) or
+//                      8-byte (fp16/bf16) write;
+// gen_normal16_kernel  4 million and more 16-bit normals: a binary32 first
+//                      pass on a persistent grid, binary64 where it is not
+//                      sure (the same bits);
+// t3_kernel            one thread per Student-t value (a block each);
+// perturb_kernel       planted changes, 16 bytes per thread.
+// The work is bound by instruction issue (ten 32x32->64 multiply rounds per
+// block, plus the logarithm, root, sine and cosine per normal pair).
 #include <algorithm>
 
 #include "kb_device.hpp"
@@ -123,18 +131,18 @@ __global__ __launch_bounds__(256) void gen_kernel(void* __restrict__ dst, uint64
 }
 
 // Normals stored in 16 bits.  The values are defined by the binary64 transform
-// rounded to binary32, scaled, and rounded again to 16 bits; only one in some
-// hundred of them lies close enough to a rounding boundary for more than 20
-// bits of the normal to matter.  So each normal is first formed in binary32
-// (rho32 and sincos32: the binary32 steps issue no faster than binary64's
-// here, but a pair takes 40 of them instead of 75) as an interval.  The errors
-// are relative -- rho 2^-22.6, the sine or cosine 2^-22.3, their product and
-// the definition's own rounding to binary32 2^-24 each, 2^-21.0 in all -- so
-// the binary32 normal lies between z (1 - e) and z (1 + e), e = 1.25 * 2^-21
-// (the two products' rounding included), and since the scaling and the
-// rounding are monotone, an interval whose two ends are stored as the same
-// bits stores the value's bits.  A
-// block with any other interval is put on the work-group's list and computed
+// rounded to binary32, scaled, and rounded again to 16 bits; only about one in
+// 600 fp16 values (one in eight times as many of bf16) lies close enough to a
+// rounding boundary for more than 20 bits of the normal to matter, 2.5 in 100
+// blocks of four at the worst shift (p0 = -p1).  So each normal is first formed
+// in binary32 (rho32 and sincos32: the binary32 steps issue no faster than
+// binary64's here, but a pair takes 40 of them instead of 75) as an interval.
+// The errors are relative -- rho 2^-22.2 at most, the sine or cosine 2^-22.3,
+// their product 2^-24, 7.7 units of 2^-24 in all -- so the definition's normal
+// lies between z (1 - e) and z (1 + e), e = 1.25 * 2^-21 (10 units), and since
+// its rounding to binary32, the scaling and the last rounding are monotone, an
+// interval whose two ends are stored as the same bits stores the value's bits.
+// A block with any other interval is put on the work-group's list and computed
 // by the binary64 path after the loop, when the list fills whole waves: the
 // outputs are the same bits as without the first pass.  Bound by instruction
 // issue: 3 x 33.5 million fp16 values 157 -> 105 us.
@@ -234,7 +242,9 @@ hipError_t launch_typed(void* dst, uint64_t n, float p0, float p1, uint64_t seed
     if constexpr (DIST == KB_DIST_NORMAL && DT != DT_F32) {
         if ((offset & 3u) == 0 && n_blocks >= kNormal16Blocks) {
             // up to 256 blocks a thread, so that the list (about one block in
-            // 150 of fp16, fewer of bf16) stays well under its length
+            // 150 of fp16, fewer of bf16) stays well under its length; at the
+            // worst shift it can fill, and its last blocks are computed in
+            // place
             const uint64_t grid16 = std::max<uint64_t>(kNormal16Grid, (want + 255) / 256);
             hipLaunchKernelGGL((gen_normal16_kernel<DT>), dim3((unsigned)std::min(want, grid16)), dim3(256), 0, stream,
                                dst, n, p0, p1, (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, sub, b_first);

@@ -1,5 +1,5 @@
-// kb_math.hpp -- binary64 logarithm, square root, sine / cosine and
-// exponential for the seeded generator.
+// kb_math.hpp -- binary64 logarithm, square root and sine / cosine for the
+// seeded generator, and their binary32 forms for 16-bit outputs.
 //
 // The generator's arguments are 32-bit words mapped to (0, 1] and [0, 2 pi),
 // so none of what a general library function carries is needed: no
@@ -7,10 +7,11 @@
 // Box-Muller pair takes about 70 binary64 operations this way, where the
 // general functions took about 300 (the generator is bound by instruction
 // issue, not by memory; 3 x 33.5 million fp16 normals: 297 -> 170 us, the
-// Student-t of 16.8 million elements: 245 -> 150 us).  Each function is
-// within 2.6 units in the last place of binary64, so the binary32 rounding of
-// a result moves about as rarely as between two general libraries (a few in
-// 10^8).
+// Student-t of 16.8 million elements, taken literally: 245 -> 150 us).  The
+// logarithm, root, sine and cosine are within 2.6 units in the last place of
+// binary64, the Student-t within 4.4, so the binary32 rounding of a result
+// moves about as rarely as between two general libraries: a few values in 10^8
+// differ by one unit in the last place of binary32 from what those gave.
 //
 // Method: argument reduction, then a polynomial whose coefficients are the
 // minimax ones of the stated function on the stated interval (computed by
@@ -20,7 +21,8 @@
 // rounding).
 //
 // Plain C++: the host can compile it too (a Seed type supplies the seeds), so
-// the error bounds are checked on the CPU at the ends of every interval.
+// the error bounds are checked on the CPU, at the ends of every interval and on
+// words spread over the range.
 #pragma once
 
 #include <stdint.h>
@@ -131,10 +133,12 @@ KB_MATH void box_muller64(uint32_t xa, uint32_t xb, double& zc, double& zs) {
 // hardware (v_log_f32), and the rounding of u put back to first order where
 // it matters: log2(u) - log2(f 2^-32) = lo log2(e) / v, lo = v - f, with
 // 1 / u taken as 2 - u (exact to (1 - u)^2 where the logarithm goes to zero;
-// below u = 1/2 the term is under 2^-24 of the logarithm anyway).
-// Largest error over all 2^32 words, against the binary64 functions: rho
-// 2^-22.6 of its value wherever it is sure (1 - u above 2^-23), sin and cos
-// 2^-22.3.
+// below u = 1/2 the term is under 2^-24 of the logarithm anyway).  Sure where
+// 1 - u is above about 2^-21.5.
+// Largest error over all 2^32 words on the device, against the binary64
+// functions: rho 2^-22.6 of its value wherever it is sure, sin and cos 2^-22.3;
+// on the host rho 2^-22.9 with the logarithm and the root as rounded, 2^-22.2
+// with both off by one unit in the last place.
 template <class Seed>
 KB_MATH float rho32(uint32_t x, bool& sure) {
     const uint32_t v = x + 1u;  // (0 for u = 1: f = 0, not sure)

@@ -4,6 +4,10 @@
 // over the range.  The seeds are off by 2^-23 either way, twice what the
 // device's reciprocal and inverse square root instructions may be off.
 // Prints one line per function: name, largest error, word (pair) it was at.
+// With an argument instead: the binary32 functions of the 16-bit first pass
+// (rho32, sincos32) where they are sure, against binary64, as relative errors
+// in units of 2^-24; rho32 with the logarithm and the root as rounded, then
+// both one unit in the last place too large, and too small.
 #include <cmath>
 #include <cstdio>
 #include <vector>
@@ -20,6 +24,12 @@ struct Seed {
     static double frexp_mant(double x) { int e; return std::frexp(x, &e); }
     static int frexp_exp(double x) { int e; std::frexp(x, &e); return e; }
     static double ldexp(double x, int n) { return std::ldexp(x, n); }
+    // binary32: correctly rounded, then off by one unit in the last place
+    // (SIGN 0: as rounded), as the device's logarithm and root may be
+    static float step(float x) { return SIGN == 0 ? x : std::nextafter(x, SIGN > 0 ? INFINITY : -INFINITY); }
+    static uint32_t to_u32(float x) { return x >= 0x1p32f ? 0xFFFFFFFFu : (uint32_t)x; }
+    static float log2(float x) { return step((float)std::log2((double)x)); }
+    static float sqrt32(float x) { return step((float)std::sqrt((double)x)); }
 };
 
 // |got - want| in units in the last place of binary64 at want.
@@ -82,7 +92,45 @@ void check(const std::vector<uint32_t>& words) {
 
 }  // namespace
 
-int main() {
+// The largest relative errors of the binary32 functions, over every 61st word
+// and all words next to the multiples of 1/8 turn and the ends of the range.
+template <int SIGN>
+void check32() {
+    double rho = 0.0, angle = 0.0;
+    uint32_t rho_at = 0, angle_at = 0;
+    auto see = [&](uint32_t x) {
+        bool sure;
+        const float r = kb::rho32<Seed<SIGN>>(x, sure);
+        if (sure) {
+            const double u = ((double)x + 1.0) * 0x1p-32;
+            const double want = std::sqrt(-2.0 * (u > 0.75 ? std::log1p(((double)x + 1.0 - 0x1p32) * 0x1p-32) : std::log(u)));
+            const double e = std::fabs((double)r - want) / want;
+            if (!(e <= rho)) { rho = e; rho_at = x; }
+        }
+        if (SIGN != 0) return;
+        float s, c;
+        kb::sincos32(x, s, c, sure);
+        if (sure) {
+            const double theta = 6.283185307179586476925286766559 * ((double)x * 0x1p-32);
+            const double e = std::fmax(std::fabs((s - std::sin(theta)) / std::sin(theta)),
+                                       std::fabs((c - std::cos(theta)) / std::cos(theta)));
+            if (!(e <= angle)) { angle = e; angle_at = x; }
+        }
+    };
+    for (uint64_t x = 0; x < (1ull << 32); x += 61) see((uint32_t)x);
+    for (uint32_t o = 0; o < 8; ++o)
+        for (int32_t d = -100000; d <= 100000; ++d) see((o << 29) + (uint32_t)d);
+    std::printf("rho32 %.3f %08x\n", rho * 0x1p24, rho_at);
+    if (SIGN == 0) std::printf("sincos32 %.3f %08x\n", angle * 0x1p24, angle_at);
+}
+
+int main(int argc, char**) {
+    if (argc > 1) {  // the binary32 functions only
+        check32<0>();
+        check32<1>();
+        check32<-1>();
+        return 0;
+    }
     std::vector<uint32_t> words;
     // every power of two and every eighth of the circle, with neighbours
     for (int k = 0; k < 32; ++k)

@@ -120,6 +120,37 @@ def test_normal_16bit_first_pass(dev, dt, n, offset, p0, p1):
     assert torch.equal(got.view(torch.int16), f.to(got.dtype).view(torch.int16))
 
 
+@pytest.mark.parametrize("dt", ["f16", "bf16"])
+@pytest.mark.parametrize("seed,sid,sub,offset", [(0, 0, 0, 0), (1, 0x100, 1, 1 << 20), (0x123456789ABCDEF, 9, 7, 1 << 40),
+                                                 (2 ** 64 - 1, 2 ** 32 - 1, 2 ** 32 - 1, 0), (42, 0x200, 3, (1 << 61) + 8),
+                                                 (7, 0x402, 0, 1 << 33)])
+def test_normal_16bit_first_pass_streams(dev, dt, seed, sid, sub, offset):
+    """The first pass over six streams of 2^26 values: some 10^8 word pairs
+    of each type, no two alike."""
+    n = 1 << 26
+    print("normal first pass, streams", dt, seed, sid, sub, offset, flush=True)
+    f = torch.empty(n, dtype=torch.float32, device=dev)
+    kb.kb_gen_inputs(f, kb.KB_DIST_NORMAL, 0.0, 1.0, seed=seed, stream_id=sid, sub=sub, offset=offset)
+    got = torch.empty(n, dtype={"f16": torch.float16, "bf16": torch.bfloat16}[dt], device=dev)
+    kb.kb_gen_inputs(got, kb.KB_DIST_NORMAL, 0.0, 1.0, seed=seed, stream_id=sid, sub=sub, offset=offset)
+    assert torch.equal(got.view(torch.int16), f.to(got.dtype).view(torch.int16))
+
+
+def test_normal_16bit_first_pass_full_list(dev):
+    """With p0 = -p1 about one fp16 block in 40 is not sure (values near zero
+    have boundaries as fine as the normal's error): at 256 blocks a thread
+    some 1,600 a work-group, past the 1,024 that its list holds."""
+    n = 1 << 29
+    print("normal first pass, full list", n, flush=True)
+    f = torch.empty(n, dtype=torch.float32, device=dev)
+    kb.kb_gen_inputs(f, kb.KB_DIST_NORMAL, -1.0, 1.0, seed=3, stream_id=5, sub=2)
+    got = torch.empty(n, dtype=torch.float16, device=dev)
+    kb.kb_gen_inputs(got, kb.KB_DIST_NORMAL, -1.0, 1.0, seed=3, stream_id=5, sub=2)
+    step = 1 << 26
+    for a in range(0, n, step):
+        assert torch.equal(got[a:a + step].view(torch.int16), f[a:a + step].to(torch.float16).view(torch.int16)), a
+
+
 @pytest.mark.parametrize("dist,dt,n", [("normal", "f32", 1 << 30), ("uniform", "f32", 1 << 30),
                                        ("normal", "bf16", 4096 * 4096), ("u32", "u32", 1 << 28)])
 def test_full_size_sampled(dev, dist, dt, n):
