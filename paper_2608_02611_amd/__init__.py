@@ -274,10 +274,13 @@ def describe(t, dtype=None):
 def _stream_handle(stream=None):
     if stream is not None:
         return ctypes.c_void_p(stream.cuda_stream)
-    # the handle alone: torch.cuda.current_stream() also makes a Stream object,
-    # which took 2.7 us of a call's 8
+    # the handle alone where torch gives it: torch.cuda.current_stream() also
+    # makes a Stream object, which took 2.7 us of a call's 8
     torch = _torch()
-    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(raw(torch.cuda.current_device()))
 
 
 # ------------------------------------------------------------- interface ---

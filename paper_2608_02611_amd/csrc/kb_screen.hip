@@ -1399,6 +1399,13 @@ __global__ void records_only_kernel(const CandEntry* uploaded, InlineTable tab, 
     }
 }
 
+// (late_params reads the first kernel argument)
+template <class First, class... Rest>
+constexpr bool first_is_params(void (*)(First, Rest...)) {
+    return __is_same(First, ScreenParams);
+}
+static_assert(first_is_params(screen_kernel<DT_F32, 1, false, false, false>));
+
 // Variants: 0 plain, 1 fail-fast, 2 positions.
 enum Variant : int { V_PLAIN = 0, V_FF, V_LOC };
 

@@ -5,6 +5,7 @@ import os
 import re
 
 import pytest
+import torch
 
 import paper_2608_02611_amd as kb
 from tests.helpers import ensure_built
@@ -600,3 +601,18 @@ def test_error_text_belongs_to_the_calling_thread(L):
         futs = [ex.submit(failing if t % 2 == 0 else succeeding, t) for t in range(8)]
         bad = [f.result() for f in futs if f.result() is not None]
     assert not bad, bad
+
+
+def test_stream_handle_without_the_raw_call(monkeypatch):
+    """The current stream's handle where this torch has no call for the handle
+    alone (a private one), and with it."""
+    class Stream:
+        cuda_stream = 0x1234
+
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda d: 0x5670 + d, raising=False)
+    assert kb._stream_handle().value == 0x5673
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    assert kb._stream_handle().value == 0x1234
+    assert kb._stream_handle(Stream).value == 0x1234
