@@ -131,10 +131,12 @@ __device__ __forceinline__ float elem(const Raw<DT>& x, int i) {
 // same one rounding, zeros and special values included), where a conversion
 // and a subtraction issue for half as long again.  Fail-fast screens of 64 x
 // 2^24 values 227 -> 218 us, 31 x 2^24 164 -> 153, 16 x 2^25 144 -> 132; plain
-// ones wait for memory (16 x 2^25 175, 174; 64 x 2^24 334 either way).
-template <int DT>
+// ones wait for memory: groups of 8 the same or a little faster (100 x 2^20 45.6
+// -> 44.8), smaller ones keep the two instructions (the two-output attention
+// screen, in groups of 4, 189.8 us, 191.8 with the one).
+template <int DT, bool ONE>
 __device__ __forceinline__ float elem_minus(const Raw<DT>& x, int i, float r) {
-    if constexpr (DT == DT_F16) {
+    if constexpr (DT == DT_F16 && ONE) {
         float s;
         if (i & 1)
             asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,0] op_sel_hi:[1,0,0]"
@@ -831,7 +833,7 @@ __device__ __forceinline__ void screen_part(const ScreenParams& p, const InlineT
             float tmax = 0.f, acc = 0.f;
 #pragma unroll
             for (int i = 0; i < kE; ++i) {
-                s[i] = elem_minus<DT>(cr, i, r[i]);
+                s[i] = elem_minus<DT, FF || KG >= 8>(cr, i, r[i]);
                 nmatch += count_within(s[i], tol[i]);
                 tmax = fmaxf(tmax, fabsf(s[i]));
                 acc = fmaf(s[i], s[i], acc);
