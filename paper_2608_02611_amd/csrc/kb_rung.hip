@@ -122,16 +122,19 @@ __device__ __forceinline__ void wave_sort(uint64_t v[E], int lane) {
 }
 
 // A row held by a wave: sample 64 e + lane in v[e], positive infinity past
-// the end; whether all n samples are valid.
+// the end.
 template <int E>
-__device__ __forceinline__ bool load_row(const double* t, int n, int lane, double v[E]) {
+__device__ __forceinline__ void load_row(const double* t, int n, int lane, double v[E]) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) v[e] = 64 * e + lane < n ? t[64 * e + lane] : __builtin_inf();
+}
+
+// Whether all its n samples are valid.
+template <int E>
+__device__ __forceinline__ bool row_ok(const double v[E], int n, int lane) {
     bool bad = false;
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int i = 64 * e + lane;
-        v[e] = i < n ? t[i] : __builtin_inf();
-        bad |= i < n && !sample_ok(v[e]);
-    }
+    for (int e = 0; e < E; ++e) bad |= 64 * e + lane < n && !sample_ok(v[e]);
     return __builtin_amdgcn_ballot_w64(bad) == 0;
 }
 
@@ -168,13 +171,15 @@ __device__ __forceinline__ void row_sums(const double a[E], const double b[E], i
 // are one each, spread over the lanes.
 // 1024 candidates x 3 shapes x 60 samples: rows and scores apart 7.4 + 6.2 us
 // and a launch, this kernel 9.5 us; the promotion's batched loads 8.5 -> 5.9.
-// With scores NULL only the rows are formed.
+// With scores NULL only the rows are formed.  LOOP: a work-group takes several
+// candidates (or rows alone); without it the baseline is always summed beside
+// the row (its own row again where there is none).
 constexpr int kFusedShapes = 4096;      // 64 KB of LDS
 constexpr int kFusedWaves = 16;         // waves of a work-group at most
 constexpr int kFusedCandidates = 8192;  // (see launch_rung_stats)
 constexpr int kWaveSamples = 4;         // samples per lane at most
 
-template <int E>
+template <int E, bool LOOP>
 __global__ __launch_bounds__(64 * kFusedWaves) void rung_kernel(RungParams p, const double* __restrict__ samples,
                                                                 kb_sample_stats* __restrict__ rows,
                                                                 kb_rung_score* __restrict__ scores) {
@@ -185,16 +190,19 @@ __global__ __launch_bounds__(64 * kFusedWaves) void rung_kernel(RungParams p, co
     double* const s_base = s_mean + S;
     const double nan = __builtin_nan("");
     for (int c = blockIdx.x; c < p.n_cands; c += gridDim.x) {
-        const bool first = c == (int)blockIdx.x;
+        const bool first = !LOOP || c == (int)blockIdx.x;
         for (int s = threadIdx.x >> 6; s < S; s += blockDim.x >> 6) {
             const size_t row = (size_t)c * S + s;
-            double v[E];
-            const bool valid = load_row<E>(samples + row * (size_t)n, n, lane, v);
+            const bool with_base = !LOOP || (first && p.base >= 0);
+            double v[E], b[E];
+            load_row<E>(samples + row * (size_t)n, n, lane, v);
+            if (with_base)
+                load_row<E>(samples + (p.base >= 0 ? (size_t)p.base * S + s : row) * (size_t)n, n, lane, b);
+            const bool valid = row_ok<E>(v, n, lane);
             double sum, base_sum = 0.0;
             bool base_valid = false;
-            if (first && p.base >= 0) {
-                double b[E];
-                base_valid = load_row<E>(samples + ((size_t)p.base * S + s) * (size_t)n, n, lane, b);
+            if (with_base) {
+                base_valid = row_ok<E>(b, n, lane) && p.base >= 0;
                 row_sums<E, true>(v, b, n, lane, sum, base_sum);
             } else {
                 row_sums<E, false>(v, v, n, lane, sum, base_sum);
@@ -227,8 +235,8 @@ __global__ __launch_bounds__(64 * kFusedWaves) void rung_kernel(RungParams p, co
             const double num = lane == 0 ? sum : lane == 8 ? base_sum : q;
             const double quot = num / (lane == 0 || lane == 8 ? (double)n : q50);
             const double mean = readlane_f64(quot, 0);
-            double base_mean = nan;
-            if (p.base >= 0) base_mean = !first ? s_base[s] : base_valid ? readlane_f64(quot, 8) : nan;
+            double base_mean = base_valid ? readlane_f64(quot, 8) : nan;
+            if (!first && p.base >= 0) base_mean = s_base[s];
             double word = lane >= 1 && lane <= 4 ? q : quot;
             if (lane == 8) word = base_mean / mean;
             if (!valid) word = nan;
@@ -240,7 +248,7 @@ __global__ __launch_bounds__(64 * kFusedWaves) void rung_kernel(RungParams p, co
                 if (first) s_base[s] = base_mean;
             }
         }
-        if (scores == nullptr) continue;
+        if (LOOP && scores == nullptr) continue;
         __syncthreads();
         if (threadIdx.x < 64) {
             // lane 0: the candidate, lane 1: the baseline.  Latency: the mean of
@@ -266,6 +274,7 @@ __global__ __launch_bounds__(64 * kFusedWaves) void rung_kernel(RungParams p, co
             if (lane == 3) word = __builtin_bit_cast(double, (uint64_t)(own_ok ? 1u : 0u));
             if (lane < 4) ((double*)&scores[c])[lane] = word;
         }
+        if (!LOOP || c + (int)gridDim.x >= p.n_cands) return;
         __syncthreads();
     }
 }
@@ -479,9 +488,13 @@ hipError_t launch_rung_kernel(const RungParams& p, const double* samples, kb_sam
     const int each = (int64_t)p.n_cands * waves >= 16384 ? 2 : 1;
     const dim3 grid((p.n_cands + each - 1) / each), block(64 * waves);
     const size_t lds = 2 * sizeof(double) * (size_t)p.n_shapes;
-    if (p.n_iter <= 64) hipLaunchKernelGGL(rung_kernel<1>, grid, block, lds, stream, p, samples, rows, scores);
-    else if (p.n_iter <= 128) hipLaunchKernelGGL(rung_kernel<2>, grid, block, lds, stream, p, samples, rows, scores);
-    else hipLaunchKernelGGL(rung_kernel<4>, grid, block, lds, stream, p, samples, rows, scores);
+    const bool loop = each > 1 || scores == nullptr;
+    const auto launch = [&](auto one, auto several) {
+        hipLaunchKernelGGL(loop ? several : one, grid, block, lds, stream, p, samples, rows, scores);
+    };
+    if (p.n_iter <= 64) launch(rung_kernel<1, false>, rung_kernel<1, true>);
+    else if (p.n_iter <= 128) launch(rung_kernel<2, false>, rung_kernel<2, true>);
+    else launch(rung_kernel<4, false>, rung_kernel<4, true>);
     return hipGetLastError();
 }
 
@@ -491,7 +504,8 @@ hipError_t launch_rung_kernel(const RungParams& p, const double* samples, kb_sam
 //   up to 64 samples the one launch is the fastest (1 x 1 x 60 5.2, 6.7, 8.1;
 //     1 x 64 x 60 33, 44, 48; 4 x 1000 x 60 486, 666, 679; 8000 x 4 x 60 44 and
 //     46 before) except for very many candidates, where the scores take 64
-//     lanes each in it and one lane apart (16384 x 3 x 60 67, 55; 62 before);
+//     lanes each in it and one lane apart (16384 x 3 x 60 67, 55; 62 before;
+//     16384 x 3 x 16 37, 36; 8193 x 2 x 1 12, 16);
 //   65 to 128: a row takes a wave 7 us, so few candidates with many rows per
 //     wave are better spread over the device (16 x 20 x 128 21, 26, 26;
 //     1 x 48 x 128 48, 37, 36; but 64 x 64 x 128 64, 72, 84);
@@ -504,7 +518,7 @@ hipError_t launch_rung_stats(const RungParams& p, const double* samples, kb_samp
     const int n_rows = p.n_cands * p.n_shapes;
     int per_wave;
     rung_waves(p, &per_wave);
-    const bool fits = p.n_shapes <= kFusedShapes && p.n_cands <= kFusedCandidates;
+    const bool fits = p.n_shapes <= kFusedShapes && (p.n_cands <= kFusedCandidates || p.n_iter <= 16);
     bool fused, by_wave;  // one launch; else rows by rung_kernel
     if (p.n_iter <= 64) fused = fits, by_wave = true;
     else if (p.n_iter <= 128) fused = fits && (per_wave <= 2 || p.n_cands >= 64), by_wave = true;
